@@ -1433,57 +1433,119 @@ int sv_probabilities(sv_handle h, const int *qubits, int m, double *out)
     return SV_OK;
 }
 
+// Expectation value of a string with ny Y from the one-value kernels' V:
+// i^ny V for even ny, i^ny (i V) for odd ny.
+static double pauli_value(double v, int ny)
+{
+    return ((ny + (ny & 1)) & 2) ? -v : v;
+}
+
 // Expectation values of parsed Pauli strings (x mask, y|z mask, number of
 // Y) on the handle's stream: d_part holds the launches' partial sums
 // (expect_scratch_doubles), d_res 2 * nterms result doubles, h_res as many
-// host doubles (pinned or not), order[nterms] an index buffer.  Device
-// results: the Z-only strings first (one double each, in order of
-// appearance), then (Re, Im) of each general string.  Every launch is
-// queued, then one copy and one wait.
+// host doubles (pinned or not), order[nterms] an index buffer.  Every launch
+// is queued, then one copy and one wait.  Device results follow `order`: one
+// double per string, two (Re, Im) for a string flagged kPair.
+//  - Small states (2^kExpectMultiMax amplitudes, in cache): all strings in one
+//    launch per expect_multi_batch().
+//  - Z strings: up to expect_z_batch() by the sweep that adds each string up
+//    (2^28 complex64 amplitudes, 8 strings: 0.327 ms a call against 0.356 by
+//    the Walsh kernel), more by the Walsh kernel, expect_walsh_batch() per
+//    read (16 strings of 2^24: 47 us against 72 with the adding sweep).
+//  - General strings: as many as share a tile in one read; a string that
+//    shares it with no other by its own sweep over the pairs.
 static int expect_core(sv_state *h, int nterms, const uint64_t *xs, const uint64_t *yzs, const int *nys,
                        double *d_part, double *d_res, double *h_res, int *order, double *out)
 {
+    constexpr int kB = 128;  // strings of one launch
+    constexpr int kPair = 1 << 30;
+    uint64_t bx[kB], byz[kB];
+    int bny[kB];
+    auto gather = [&](int first, int count) {
+        for (int j = 0; j < count; ++j) {
+            const int t = order[first + j];
+            bx[j] = xs[t];
+            byz[j] = yzs[t];
+            bny[j] = nys[t];
+        }
+    };
+    auto check = [](hipError_t e) -> int {
+        if (e == hipSuccess)
+            return SV_OK;
+        set_error("Pauli expectation launch failed: %s", hipGetErrorString(e));
+        return SV_EDEVICE;
+    };
     int nz = 0;
     for (int t = 0; t < nterms; ++t)
         if (xs[t] == 0)
             order[nz++] = t;
-    int nxy = 0;
-    for (int t = 0; t < nterms; ++t)
+    for (int t = 0, j = nz; t < nterms; ++t)
         if (xs[t] != 0)
-            order[nz + nxy++] = t;
-    constexpr int kZ = 64;
-    const int zb = std::min(expect_z_batch(), kZ);
-    for (int s = 0; s < nz; s += zb) {
-        const int nb = std::min(zb, nz - s);
-        uint64_t z[kZ];
-        for (int j = 0; j < nb; ++j)
-            z[j] = yzs[order[s + j]];
-        hipError_t e = launch_expect_z(h->d_state, h->n, h->dtype, z, nb, d_part, d_res + s, h->stream);
-        if (e != hipSuccess) {
-            set_error("Z expectation launch failed: %s", hipGetErrorString(e));
-            return SV_EDEVICE;
+            order[j++] = t;
+    int rc = SV_OK;
+    size_t nres = 0;
+    if (h->n <= kExpectMultiMax) {
+        const int mb = std::min(expect_multi_batch(), kB);
+        for (int s = 0; s < nterms && rc == SV_OK; s += mb) {
+            const int nb = std::min(mb, nterms - s);
+            gather(s, nb);
+            rc = check(launch_expect_multi(h->d_state, h->n, h->dtype, bx, byz, bny, nb, d_part, d_res + s,
+                                           h->stream));
+        }
+        nres = size_t(nterms);
+    } else {
+        const bool walsh = nz > expect_z_batch();
+        const int zb = std::min(walsh ? expect_walsh_batch() : expect_z_batch(), kB);
+        for (int s = 0; s < nz && rc == SV_OK; s += zb) {
+            const int nb = std::min(zb, nz - s);
+            gather(s, nb);
+            rc = check(walsh ? launch_expect_walsh(h->d_state, h->n, h->dtype, byz, nb, d_part, d_res + s, h->stream)
+                             : launch_expect_z(h->d_state, h->n, h->dtype, byz, nb, d_part, d_res + s, h->stream));
+        }
+        nres = size_t(nz);
+        const int T = expect_tile_bits(h->dtype), tb = std::min(expect_tile_batch(), kB);
+        for (int p = nz; p < nterms && rc == SV_OK;) {
+            // order[p, p + nb): strings that share a tile with order[p]
+            uint64_t bits = expect_tile_low(h->dtype);
+            int nb = 0;
+            for (int j = p; j < nterms && nb < tb; ++j) {
+                const uint64_t u = bits | xs[order[j]];
+                if (__builtin_popcountll(u) <= T) {
+                    bits = u;
+                    std::swap(order[p + nb], order[j]);
+                    ++nb;
+                }
+            }
+            if (nb >= 2) {
+                gather(p, nb);
+                rc = check(launch_expect_tile(h->d_state, h->n, h->dtype, bx, byz, bny, nb, d_part, d_res + nres,
+                                              h->stream));
+                nres += size_t(nb);
+                p += nb;
+            } else {
+                // alone: whatever order[p] is now (nb = 1 leaves it in place)
+                const int t = order[p];
+                rc = check(launch_expect_xy(h->d_state, h->n, h->dtype, xs[t], yzs[t], d_part, d_res + nres,
+                                            h->stream));
+                nres += 2;
+                order[p++] = t | kPair;
+            }
         }
     }
-    for (int q = 0; q < nxy; ++q) {
-        const int t = order[nz + q];
-        hipError_t e = launch_expect_xy(h->d_state, h->n, h->dtype, xs[t], yzs[t], d_part, d_res + nz + 2 * q,
-                                        h->stream);
-        if (e != hipSuccess) {
-            set_error("Pauli expectation launch failed: %s", hipGetErrorString(e));
-            return SV_EDEVICE;
-        }
-    }
-    const size_t nres = size_t(nz) + 2 * size_t(nxy);
+    if (rc != SV_OK)
+        return rc;
     HIP_TRY(hipMemcpyAsync(h_res, d_res, nres * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
-    for (int j = 0; j < nz; ++j)
-        out[order[j]] = h_res[j];
     static const cd ipow[4] = {cd(1, 0), cd(0, 1), cd(-1, 0), cd(0, -1)};
-    for (int q = 0; q < nxy; ++q) {
-        const int t = order[nz + q];
-        const cd S(h_res[nz + 2 * q], h_res[nz + 2 * q + 1]);
-        // multiply by i^(number of Y)
-        out[t] = (ipow[nys[t] & 3] * S).real();
+    const double *r = h_res;
+    for (int j = 0; j < nterms; ++j) {
+        const int t = order[j] & ~kPair;
+        if (order[j] & kPair) {
+            out[t] = (ipow[nys[t] & 3] * cd(r[0], r[1])).real();
+            r += 2;
+        } else {
+            out[t] = pauli_value(*r++, nys[t]);
+        }
     }
     return SV_OK;
 }

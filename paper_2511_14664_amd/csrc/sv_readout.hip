@@ -205,8 +205,9 @@ static hipError_t launch_sum_rows(const double *part, double *out, uint64_t rows
 namespace {
 
 // ---------------------------------------------------------------------------
-// Z-string expectations: sum_i |a_i|^2 (-1)^popcount(i & z_t), up to kMaxZ
-// strings per pass.  part[t * gridDim + block].
+// Z-string expectations: sum_i |a_i|^2 (-1)^popcount(i & z_t), up to kFewZ
+// strings per pass (more go through the Walsh kernel below).
+// part[t * gridDim + block].
 //
 // A thread visits the indexes h0 + 256 u + threadIdx.x, u < 16, with h0 a
 // multiple of 4096 that is the same across the workgroup, so the sign
@@ -220,18 +221,19 @@ namespace {
 // and string the work is one FP64 FMA with a scalar +-1 operand (the scalar
 // unit, shared by a CU's four SIMDs, otherwise bounds the sweep).
 // ---------------------------------------------------------------------------
-constexpr int kMaxZ = 32;
+constexpr int kMaxZ = 32;  // strings of one fused read-out
+constexpr int kFewZ = 8;
 struct ExpZArgs {
     uint64_t nelem;
     int nt;
-    uint64_t z[kMaxZ];
+    uint64_t z[kFewZ];
 };
 
 template <typename R, int NZ>
 __global__ __launch_bounds__(kThreads) void k_expect_z(const R *__restrict__ st, double *__restrict__ part,
                                                        const ExpZArgs a)
 {
-    static_assert(NZ <= 64 && NZ <= kMaxZ, "one string per lane");
+    static_assert(NZ <= 64 && NZ <= kFewZ, "one string per lane");
     using C = typename CT<R>::C;
     constexpr int LU = 4, U = 1 << LU;  // amplitudes per thread and step: index bits 8 .. 11
     static_assert(kThreads == 256, "lane and wave bits 0 .. 7");
@@ -328,6 +330,339 @@ __global__ __launch_bounds__(kThreads) void k_expect_xy(const R *__restrict__ st
         part[blockIdx.x] = sre;
         part[uint64_t(gridDim.x) + blockIdx.x] = sim;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Several general strings from one read: one value per string,
+//     V = sum_i s(i) f(a_i, a_{i ^ x}),   s(i) = (-1)^popcount(i & yz),
+// f = Re(conj(a_j) a_i) for an even number of Y, Im for an odd one: with
+// s(i ^ x) = (-1)^#Y s(i), the other part of S cancels between i and i ^ x
+// (S = V, or i V), so only one FP64 product sum is taken per string.
+// ---------------------------------------------------------------------------
+struct PauliTerm {
+    uint64_t x;
+    uint64_t yz;
+    uint32_t odd;  // number of Y is odd
+    uint32_t pad;
+};
+
+// (p, q) with f = p b.x + q b.y for the partner amplitude b of a.
+template <typename C>
+__device__ __forceinline__ void pauli_weights(C a, bool odd, double &p, double &q)
+{
+    p = odd ? double(a.y) : double(a.x);
+    q = odd ? -double(a.x) : double(a.y);
+}
+
+// Small states: block (chunk, string), every string reads its chunk of the
+// pairs (i, i ^ x) from cache; one launch for all strings, Z strings included
+// (x = 0: every amplitude its own partner).  With one chunk part is the result.
+constexpr int kMultiTerms = 128;
+struct ExpMultiArgs {
+    uint64_t per_chunk;  // pairs (amplitudes for x = 0: twice that) per block
+    PauliTerm t[kMultiTerms];
+};
+
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_expect_multi(const R *__restrict__ st, double *__restrict__ part,
+                                                           const ExpMultiArgs a)
+{
+    using C = typename CT<R>::C;
+    __shared__ double sh[4];
+    const C *v = reinterpret_cast<const C *>(st);
+    const PauliTerm t = a.t[blockIdx.y];
+    double acc = 0.0;
+    if (t.x == 0) {
+        const uint64_t i0 = uint64_t(blockIdx.x) * 2 * a.per_chunk;
+        for (uint64_t e = threadIdx.x; e < 2 * a.per_chunk; e += kThreads) {
+            const double p = prob(v[i0 + e]);
+            acc += (__popcll((i0 + e) & t.yz) & 1) ? -p : p;
+        }
+    } else {
+        const uint64_t hmask = (uint64_t(1) << (63 - __builtin_clzll(t.x))) - 1;
+        const uint64_t g0 = uint64_t(blockIdx.x) * a.per_chunk;
+        for (uint64_t e = threadIdx.x; e < a.per_chunk; e += kThreads) {
+            const uint64_t g = g0 + e;
+            const uint64_t i = (g & hmask) | ((g & ~hmask) << 1);
+            const C ai = v[i], aj = v[i ^ t.x];
+            double p, q;
+            pauli_weights(ai, t.odd != 0, p, q);
+            const double f = fma(p, double(aj.x), q * double(aj.y));
+            acc += (__popcll(i & t.yz) & 1) ? -f : f;
+        }
+        acc *= 2.0;
+    }
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0)
+        part[uint64_t(blockIdx.y) * gridDim.x + blockIdx.x] = acc;
+}
+
+// Large states: strings whose X and Y positions all lie among the index bits
+// of one LDS tile (32 KiB: 2^12 complex64 or 2^11 complex128 amplitudes, the
+// lowest bits among them so that runs are whole lines) share one read of the
+// state.  A workgroup takes tiles o = block, block + grid, ...; the next
+// tile's loads are in flight during the current one's sums.  Per string the
+// threads share the tile's pairs of 16-byte vectors (i, i ^ x), both read from
+// LDS: 15 vector instructions per four complex64 amplitudes, 8 of them
+// conversions to FP64.  They bound the sweep: three reads of 2^27 complex64
+// amplitudes with 8..12 strings each take 0.36 ms apiece (0.18 ms a read,
+// 0.18 ms per string when every string read the state by itself); complex128,
+// without conversions, 0.064 ms per read of 2^24 (0.046 ms per string before).
+// Holding every thread's own amplitudes converted instead took 7 instructions
+// per amplitude and 229 registers: 0.55 ms per read.
+constexpr int kTileTerms = 16;
+struct ExpTileArgs {
+    uint64_t ntiles;
+    uint64_t dep[12];  // physical index bit of tile bit b
+    Masks outer;
+    int nt;
+    uint32_t xl[kTileTerms];   // tile-local X|Y bits
+    uint32_t yl[kTileTerms];   // tile-local Y|Z bits
+    uint64_t yz[kTileTerms];
+    uint32_t odd[kTileTerms];
+};
+
+template <typename R>
+constexpr int expect_tile_log()
+{
+    return std::is_same<R, float>::value ? 12 : 11;
+}
+
+typedef double f64x16 __attribute__((ext_vector_type(16)));
+
+// Workgroups per CU that the registers of the persistent sweeps leave room
+// for; their grids are that many per CU, so that all are resident at once.
+template <typename R>
+constexpr int tile_per_cu()
+{
+    return std::is_same<R, float>::value ? 3 : 4;
+}
+template <typename R>
+constexpr int walsh_per_cu()
+{
+    return std::is_same<R, float>::value ? 4 : 2;
+}
+
+template <typename R>
+__global__ __launch_bounds__(kThreads, tile_per_cu<R>()) void k_expect_tile(const R *__restrict__ st, double *__restrict__ part,
+                                                          const ExpTileArgs a)
+{
+    constexpr bool F32 = std::is_same<R, float>::value;
+    using V = typename std::conditional<F32, float4, double2>::type;  // 16 bytes
+    constexpr int LO = F32 ? 1 : 0;   // tile bits inside a vector
+    constexpr int NLD = 8;            // vectors per thread: tile bits LO + 8 ..
+    __shared__ V tile[NLD * kThreads];
+    __shared__ double sh[4];
+    const V *v = reinterpret_cast<const V *>(st);
+    const int tid = threadIdx.x;
+    uint64_t off = 0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+        if ((tid >> b) & 1)
+            off |= a.dep[b + LO];
+    auto offk = [&](int k) {
+        return ((k & 1) ? a.dep[8 + LO] : 0) | ((k & 2) ? a.dep[9 + LO] : 0) | ((k & 4) ? a.dep[10 + LO] : 0);
+    };
+    f64x16 acc = {};
+    V nx[NLD];
+    uint64_t base = insert_zeros(blockIdx.x, a.outer);
+#pragma unroll
+    for (int k = 0; k < NLD; ++k)
+        nx[k] = ldnt(&v[(base | off | offk(k)) >> LO]);
+    for (uint64_t o = blockIdx.x; o < a.ntiles; o += gridDim.x) {
+        const uint64_t cur = base;
+#pragma unroll
+        for (int k = 0; k < NLD; ++k)
+            tile[k * kThreads + tid] = nx[k];
+        if (o + gridDim.x < a.ntiles) {
+            base = insert_zeros(o + gridDim.x, a.outer);
+#pragma unroll
+            for (int k = 0; k < NLD; ++k)
+                nx[k] = ldnt(&v[(base | off | offk(k)) >> LO]);
+        }
+        __syncthreads();
+        for (int t = 0; t < a.nt; ++t) {
+            const uint32_t xl = a.xl[t], yl = a.yl[t], xv = xl >> LO, yv = yl >> LO;
+            uint32_t par = 0;  // parity of this thread's part of the signs
+            // the number of Y and the swap of a vector's two amplitudes are
+            // the same for every thread: a branch, not a selection
+            auto sum = [&](auto odd_tag, auto swap_tag) __attribute__((always_inline)) {
+                constexpr bool ODD = decltype(odd_tag)::value, SWAP = decltype(swap_tag)::value;
+                // f of amplitude a and partner b
+                auto f = [](double ar, double ai, double br, double bi) __attribute__((always_inline)) {
+                    return ODD ? fma(ai, br, -(ar * bi)) : fma(ai, bi, ar * br);
+                };
+                double r = 0.0;
+                if (!SWAP || xv != 0) {
+                    // vectors i (bit h clear, or for h < 4 equal to bit 4, so that
+                    // 16 consecutive lanes meet 16 different bank groups) and i ^ xv
+                    const int h = 31 - __builtin_clz(xv);
+                    const uint32_t hm = (1u << h) - 1u;
+                    uint32_t iv = (uint32_t(tid) & hm) | ((uint32_t(tid) & ~hm) << 1);
+                    if (h < 4)
+                        iv |= ((iv >> 4) & 1u) << h;
+                    par = uint32_t(__popc(iv & yv)) & 1u;
+                    V p[4], q[4];
+                    uint32_t im[4];
+#pragma unroll
+                    for (uint32_t m = 0; m < 4; ++m) {
+                        im[m] = ((m << 8) & hm) | (((m << 8) & ~hm) << 1);
+                        p[m] = tile[iv ^ im[m]];
+                        q[m] = tile[iv ^ im[m] ^ xv];
+                    }
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        double g;
+                        if constexpr (F32) {
+                            // amplitudes e and e ^ (x & 1), the second with the sign of bit 0
+                            const double g1 = SWAP ? f(p[m].z, p[m].w, q[m].x, q[m].y) : f(p[m].z, p[m].w, q[m].z, q[m].w);
+                            const double g0 = SWAP ? f(p[m].x, p[m].y, q[m].z, q[m].w) : f(p[m].x, p[m].y, q[m].x, q[m].y);
+                            g = fma((yl & 1u) ? -1.0 : 1.0, g1, g0);
+                        } else {
+                            g = f(p[m].x, p[m].y, q[m].x, q[m].y);
+                        }
+                        r = fma((__builtin_popcount(im[m] & yv) & 1) ? -1.0 : 1.0, g, r);
+                    }
+                } else if constexpr (F32) {  // x = 1: the pair inside every vector
+                    par = uint32_t(__popc(uint32_t(tid) & yv)) & 1u;
+#pragma unroll
+                    for (uint32_t k = 0; k < NLD; ++k) {
+                        const V p = tile[k * kThreads + tid];
+                        r = fma((__builtin_popcount((k << 8) & yv) & 1) ? -1.0 : 1.0, f(p.x, p.y, p.z, p.w), r);
+                    }
+                }
+                return r;
+            };
+            const bool odd = a.odd[t] != 0, swap = F32 && (xl & 1u) != 0;
+            double s;
+            if (swap)
+                s = odd ? sum(std::true_type{}, std::true_type{}) : sum(std::false_type{}, std::true_type{});
+            else
+                s = odd ? sum(std::true_type{}, std::false_type{}) : sum(std::false_type{}, std::false_type{});
+            // both members of a pair contribute the same
+            acc[t] = fma(((__popcll(cur & a.yz[t]) & 1u) ^ par) ? -2.0 : 2.0, s, acc[t]);
+        }
+        __syncthreads();
+    }
+    for (int t = 0; t < a.nt; ++t) {
+        const double w = block_sum(acc[t], sh);
+        if (tid == 0)
+            part[uint64_t(t) * gridDim.x + blockIdx.x] = w;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Many Z strings from one read: a Walsh-Hadamard transform of every 2^12
+// segment's probabilities gives sum_i p_i (-1)^popcount(i & k) for all 4096 k
+// at once, and a string takes one of them per segment with the sign of its
+// high bits: the work per amplitude does not grow with the strings (one per
+// thread, up to kWalshTerms per launch).  Three rounds of four index bits in
+// registers, exchanged through LDS; the loads of the next segment are in
+// flight meanwhile.  Bound by the read: 2^27 complex64 amplitudes in 0.173 ms,
+// 2^24 complex128 in 0.048 ms (5.6-6.2 TB/s); 81 strings in three reads of 32
+// took 0.56 ms.  Index bits by round: the bits a thread's loads differ in
+// (c64 0, 9..11; c128 8..11), 1..4, and the remaining four.
+// ---------------------------------------------------------------------------
+constexpr int kWalshTerms = 128;
+struct ExpWalshArgs {
+    uint64_t nseg;
+    int nt;
+    uint64_t z[kWalshTerms];
+};
+
+// LDS slot of index x: bits 6..9 XORed into bits 1..4, so that lanes that
+// differ in those bits only use different banks.
+__device__ __forceinline__ uint32_t walsh_slot(uint32_t x)
+{
+    return x ^ ((x >> 5) & 30u);
+}
+
+__device__ __forceinline__ void walsh16(f64x16 &w)
+{
+#pragma unroll
+    for (int b = 1; b < 16; b <<= 1)
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (!(u & b)) {
+                const double x = w[u], y = w[u | b];
+                w[u] = x + y;
+                w[u | b] = x - y;
+            }
+}
+
+template <typename R>
+__global__ __launch_bounds__(kThreads, walsh_per_cu<R>()) void k_expect_walsh(const R *__restrict__ st, double *__restrict__ part,
+                                                           const ExpWalshArgs a)
+{
+    constexpr bool F32 = std::is_same<R, float>::value;
+    using V = typename std::conditional<F32, float4, double2>::type;  // 16 bytes
+    constexpr int SEG = 4096;
+    constexpr int NLD = F32 ? 8 : 16;
+    __shared__ __align__(16) double w_lds[SEG];
+    const V *v = reinterpret_cast<const V *>(st);
+    const int tid = threadIdx.x;
+    const uint64_t z = tid < a.nt ? a.z[tid] : 0;
+    // round 2: index bits 1..4 in registers, the thread gives the others (bit
+    // 0 and 5..11); round 3: c64 bits 5..8 in registers, the thread gives
+    // 0..4 and 9..11; c128 bits 0 and 5..7, the thread 1..4 and 8..11
+    const uint32_t g2 = (tid & 1u) | (uint32_t(tid >> 1) << 5);
+    const uint32_t g3 = F32 ? ((tid & 31u) | (uint32_t(tid >> 5) << 9)) : ((tid & 15u) << 1 | uint32_t(tid >> 4) << 8);
+    auto r3 = [](uint32_t u) { return F32 ? u << 5 : (u & 1u) | (u >> 1) << 5; };
+    double acc = 0.0;
+    V nx[NLD];
+#pragma unroll
+    for (int k = 0; k < NLD; ++k)
+        nx[k] = ldnt(&v[uint64_t(blockIdx.x) * (NLD * kThreads) + uint32_t(k * kThreads + tid)]);
+    for (uint64_t s = blockIdx.x; s < a.nseg; s += gridDim.x) {
+        f64x16 w;
+#pragma unroll
+        for (int k = 0; k < NLD; ++k) {
+            if constexpr (F32) {
+                w[2 * k] = prob(make_float2(nx[k].x, nx[k].y));
+                w[2 * k + 1] = prob(make_float2(nx[k].z, nx[k].w));
+            } else {
+                w[k] = prob(nx[k]);
+            }
+        }
+        if (s + gridDim.x < a.nseg) {
+#pragma unroll
+            for (int k = 0; k < NLD; ++k)
+                nx[k] = ldnt(&v[(s + gridDim.x) * (NLD * kThreads) + uint32_t(k * kThreads + tid)]);
+        }
+        walsh16(w);
+#pragma unroll
+        for (int k = 0; k < NLD; ++k) {
+            if constexpr (F32)  // the pair of bit 0 stays adjacent
+                *reinterpret_cast<double2 *>(&w_lds[walsh_slot(uint32_t(2 * (k * kThreads + tid)))]) =
+                    make_double2(w[2 * k], w[2 * k + 1]);
+            else
+                w_lds[walsh_slot(uint32_t(k * kThreads + tid))] = w[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u)
+            w[u] = w_lds[walsh_slot(g2 | u << 1)];
+        walsh16(w);
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u)
+            w_lds[walsh_slot(g2 | u << 1)] = w[u];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u)
+            w[u] = w_lds[walsh_slot(g3 | r3(u))];
+        walsh16(w);
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u)
+            w_lds[walsh_slot(g3 | r3(u))] = w[u];
+        __syncthreads();
+        if (tid < a.nt) {
+            const double c = w_lds[walsh_slot(uint32_t(z) & (SEG - 1))];
+            acc += (__popcll((s << 12) & z) & 1) ? -c : c;
+        }
+        __syncthreads();
+    }
+    if (tid < a.nt)
+        part[uint64_t(tid) * gridDim.x + blockIdx.x] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -632,7 +967,6 @@ __device__ __forceinline__ uint32_t deposit(uint32_t x, uint32_t mask)
 // sign applied once at the end), part[t * grid + block]; TOT, the total
 // probability of every 2^tlog consecutive segments, tot[block * 2^(F - tlog)
 // + j].
-typedef double f64x16 __attribute__((ext_vector_type(16)));
 struct ReadoutArgs {
     uint64_t z[kMaxZ];
     int nt;
@@ -1151,13 +1485,13 @@ uint64_t expect_scratch_doubles(int n)
 
 int expect_z_batch()
 {
-    return kMaxZ;
+    return kFewZ;
 }
 
 hipError_t launch_expect_z(const void *st, int n, int dtype, const uint64_t *zmasks, int nt, double *d_scratch,
                            double *d_out, hipStream_t s)
 {
-    if (nt < 1 || nt > kMaxZ)
+    if (nt < 1 || nt > kFewZ)
         return hipErrorInvalidValue;
     ExpZArgs a{};
     a.nelem = uint64_t(1) << n;
@@ -1166,23 +1500,10 @@ hipError_t launch_expect_z(const void *st, int n, int dtype, const uint64_t *zma
         a.z[t] = zmasks[t];
     const uint32_t grid = exp_grid(n);
     const dim3 g(grid), b(kThreads);
-    if (dtype == SV_C64) {
-        const float *p = (const float *)st;
-        if (nt <= 8)
-            hipLaunchKernelGGL((k_expect_z<float, 8>), g, b, 0, s, p, d_scratch, a);
-        else if (nt <= 16)
-            hipLaunchKernelGGL((k_expect_z<float, 16>), g, b, 0, s, p, d_scratch, a);
-        else
-            hipLaunchKernelGGL((k_expect_z<float, 32>), g, b, 0, s, p, d_scratch, a);
-    } else {
-        const double *p = (const double *)st;
-        if (nt <= 8)
-            hipLaunchKernelGGL((k_expect_z<double, 8>), g, b, 0, s, p, d_scratch, a);
-        else if (nt <= 16)
-            hipLaunchKernelGGL((k_expect_z<double, 16>), g, b, 0, s, p, d_scratch, a);
-        else
-            hipLaunchKernelGGL((k_expect_z<double, 32>), g, b, 0, s, p, d_scratch, a);
-    }
+    if (dtype == SV_C64)
+        hipLaunchKernelGGL((k_expect_z<float, kFewZ>), g, b, 0, s, (const float *)st, d_scratch, a);
+    else
+        hipLaunchKernelGGL((k_expect_z<double, kFewZ>), g, b, 0, s, (const double *)st, d_scratch, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -1209,6 +1530,125 @@ hipError_t launch_expect_xy(const void *st, int n, int dtype, uint64_t xmask, ui
     if (e != hipSuccess)
         return e;
     return launch_sum_rows(d_scratch, d_out2, uint64_t(2), grid, s);
+}
+
+int expect_tile_bits(int dtype)
+{
+    return dtype == SV_C64 ? expect_tile_log<float>() : expect_tile_log<double>();
+}
+
+uint64_t expect_tile_low(int dtype)
+{
+    return dtype == SV_C64 ? 15 : 7;
+}
+
+int expect_tile_batch()
+{
+    return kTileTerms;
+}
+
+int expect_multi_batch()
+{
+    return kMultiTerms;
+}
+
+int expect_walsh_batch()
+{
+    return kWalshTerms;
+}
+
+hipError_t launch_expect_multi(const void *st, int n, int dtype, const uint64_t *x, const uint64_t *yz,
+                               const int *ny, int nt, double *d_scratch, double *d_out, hipStream_t s)
+{
+    if (nt < 1 || nt > kMultiTerms || n < 1 || n > kExpectMultiMax)
+        return hipErrorInvalidValue;
+    ExpMultiArgs a{};
+    for (int t = 0; t < nt; ++t)
+        a.t[t] = PauliTerm{x[t], yz[t], uint32_t(ny[t] & 1), 0};
+    // 2^12 amplitudes (2^11 pairs) per block
+    const uint64_t chunks = n > 12 ? uint64_t(1) << (n - 12) : 1;
+    a.per_chunk = (uint64_t(1) << (n - 1)) / chunks;
+    double *part = chunks == 1 ? d_out : d_scratch;
+    const dim3 g{uint32_t(chunks), uint32_t(nt)}, b{uint32_t(kThreads)};
+    if (dtype == SV_C64)
+        hipLaunchKernelGGL(k_expect_multi<float>, g, b, 0, s, (const float *)st, part, a);
+    else
+        hipLaunchKernelGGL(k_expect_multi<double>, g, b, 0, s, (const double *)st, part, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || chunks == 1)
+        return e;
+    return launch_sum_rows(d_scratch, d_out, uint64_t(nt), uint32_t(chunks), s);
+}
+
+// Workgroups of a persistent expectation sweep over nw work items.
+static uint32_t persistent_grid(uint64_t nw, int per_cu)
+{
+    return uint32_t(std::min<uint64_t>(nw, uint64_t(256) * uint64_t(per_cu)));
+}
+
+hipError_t launch_expect_tile(const void *st, int n, int dtype, const uint64_t *x, const uint64_t *yz, const int *ny,
+                              int nt, double *d_scratch, double *d_out, hipStream_t s)
+{
+    const int T = expect_tile_bits(dtype);
+    if (nt < 1 || nt > kTileTerms || n < T)
+        return hipErrorInvalidValue;
+    uint64_t bits = expect_tile_low(dtype);
+    for (int t = 0; t < nt; ++t)
+        bits |= x[t];
+    for (int p = 0; p < n && __builtin_popcountll(bits) < T; ++p)
+        bits |= uint64_t(1) << p;
+    if (__builtin_popcountll(bits) != T || (bits >> n) != 0)
+        return hipErrorInvalidValue;
+    ExpTileArgs a{};
+    a.ntiles = uint64_t(1) << (n - T);
+    a.nt = nt;
+    int got = 0;
+    for (int p = 0; p < n; ++p) {
+        if (!((bits >> p) & 1))
+            continue;
+        a.dep[got] = uint64_t(1) << p;
+        a.outer.m[got] = (uint64_t(1) << p) - 1;
+        for (int t = 0; t < nt; ++t) {
+            a.xl[t] |= uint32_t((x[t] >> p) & 1) << got;
+            a.yl[t] |= uint32_t((yz[t] >> p) & 1) << got;
+        }
+        ++got;
+    }
+    a.outer.n = T;
+    for (int t = 0; t < nt; ++t) {
+        a.yz[t] = yz[t];
+        a.odd[t] = uint32_t(ny[t] & 1);
+    }
+    const uint32_t grid = persistent_grid(a.ntiles, dtype == SV_C64 ? tile_per_cu<float>() : tile_per_cu<double>());
+    if (dtype == SV_C64)
+        hipLaunchKernelGGL(k_expect_tile<float>, dim3(grid), dim3(kThreads), 0, s, (const float *)st, d_scratch, a);
+    else
+        hipLaunchKernelGGL(k_expect_tile<double>, dim3(grid), dim3(kThreads), 0, s, (const double *)st, d_scratch, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    return launch_sum_rows(d_scratch, d_out, uint64_t(nt), grid, s);
+}
+
+hipError_t launch_expect_walsh(const void *st, int n, int dtype, const uint64_t *zmasks, int nt, double *d_scratch,
+                               double *d_out, hipStream_t s)
+{
+    if (nt < 1 || nt > kWalshTerms || n < 12)
+        return hipErrorInvalidValue;
+    ExpWalshArgs a{};
+    a.nseg = uint64_t(1) << (n - 12);
+    a.nt = nt;
+    for (int t = 0; t < nt; ++t)
+        a.z[t] = zmasks[t];
+    const uint32_t grid = persistent_grid(a.nseg, dtype == SV_C64 ? walsh_per_cu<float>() : walsh_per_cu<double>());
+    if (dtype == SV_C64)
+        hipLaunchKernelGGL(k_expect_walsh<float>, dim3(grid), dim3(kThreads), 0, s, (const float *)st, d_scratch, a);
+    else
+        hipLaunchKernelGGL(k_expect_walsh<double>, dim3(grid), dim3(kThreads), 0, s, (const double *)st, d_scratch, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    return launch_sum_rows(d_scratch, d_out, uint64_t(nt), grid, s);
 }
 
 int sample_log_block(int n)

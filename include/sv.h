@@ -142,7 +142,9 @@ typedef struct sv_plan_opts {
 /* Counters filled by sv_apply_circuit / sv_apply_plan (may be NULL). */
 typedef struct sv_run_stats {
     int64_t gates;              /* gates of the input circuit (unfused count) */
-    int64_t sweeps;             /* kernels launched over the state */
+    int64_t sweeps;             /* sweeps over the state, one launch each; on states of at most 2^13
+                                   complex64 / 2^12 complex128 amplitudes, steps of one launch that holds
+                                   the state in LDS (unless sweeps are being timed or the stream captured) */
     int64_t fused_blocks;       /* sweeps that apply more than one gate */
     double algorithmic_bytes;   /* HBM bytes the sweeps must move (128-byte lines) */
     double flops;               /* real floating-point operations of the sweeps */

@@ -16,6 +16,7 @@ SOURCES = [
     "sv_readout.hip",
     "sv_fused_mfma.hip",
     "sv_pass.hip",
+    "sv_small.hip",
     "sv_batch.hip",
     "sv_batch_host.cpp",
     "sv_costmodel.hip",

@@ -57,6 +57,15 @@ struct PlanCacheEntry {
     std::vector<sv::PassGroup> plan;   // pass plan on the gate list with diagonal pairs pre-fused
 };
 
+// Pinned slots of a handle for programs of small states: enough for the host
+// to write the next circuits while earlier ones run, and small enough to keep.
+constexpr int kSmallSlots = 4;
+constexpr uint64_t kSmallSlotMin = 64 << 10;
+constexpr uint64_t kSmallSlotMax = 1 << 20;
+// Largest program (offsets in it are 32 bits); longer circuits keep a launch
+// per sweep, streamed in chunks.
+constexpr uint64_t kSmallMaxProgram = 64 << 20;
+
 struct sv_state {
     int n = 0;
     int dtype = 0;
@@ -80,6 +89,14 @@ struct sv_state {
     uint64_t h_arena_bytes = 0;
     hipEvent_t arena_done = nullptr;
     bool arena_pending = false;
+    // pinned slots for the programs of small states, used in turn;
+    // small_done[i] marks the last use of slot i
+    void *h_small = nullptr;
+    uint64_t small_slot_bytes = 0;
+    void *d_small = nullptr;  // device copies of the slots, for programs with large matrices
+    hipEvent_t small_done[kSmallSlots] = {};
+    bool small_pending[kSmallSlots] = {};
+    int small_next = 0;
     // plans of recent circuit structures, most recent first
     std::vector<PlanCacheEntry> plan_cache;
     // sweep timing
@@ -418,6 +435,154 @@ int run_blocks(sv_state *h, const std::vector<Block> &blocks_in, int precision, 
     return rc;
 }
 
+// Whether a circuit of nsteps sweeps runs as steps of one launch: the state
+// fits LDS, and there is more than one launch to save.  Sweeps that are timed
+// one by one keep their launches, and so does a stream that is being captured
+// (the program is read from memory that later calls reuse, while the
+// launches' arguments are part of the graph) and the BF16X3 arithmetic.
+bool small_route(sv_state *h, size_t nsteps, int precision)
+{
+    if (nsteps < 2 || !small_fits(h->n, h->dtype) || h->profiling || precision == SV_PREC_BF16X3)
+        return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs == hipStreamCaptureStatusNone;
+}
+
+// Width of the block a group becomes (fuse): a single member stays as it is.
+int group_width(const std::vector<Block> &gates, const Group &g)
+{
+    return g.members.size() == 1 ? gates[size_t(g.members[0])].k : __builtin_popcountll(g.qmask);
+}
+
+// Make the pinned slots hold programs of `bytes` each (a power of two, at most
+// kSmallSlotMax).
+int ensure_small(sv_state *h, uint64_t bytes)
+{
+    if (bytes <= h->small_slot_bytes)
+        return SV_OK;
+    for (int i = 0; i < kSmallSlots; ++i) {
+        if (!h->small_done[i])
+            HIP_TRY(hipEventCreateWithFlags(&h->small_done[i], hipEventDisableTiming));
+        if (h->small_pending[i])
+            HIP_TRY(hipEventSynchronize(h->small_done[i]));
+        h->small_pending[i] = false;
+    }
+    uint64_t want = kSmallSlotMin;
+    while (want < bytes)
+        want *= 2;
+    if (h->h_small)
+        HIP_TRY(hipHostFree(h->h_small));
+    h->h_small = nullptr;
+    if (h->d_small)
+        HIP_TRY(hipFree(h->d_small));
+    h->d_small = nullptr;
+    h->small_slot_bytes = 0;
+    if (hipHostMalloc(&h->h_small, kSmallSlots * want, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        h->h_small = nullptr;
+        set_error("cannot allocate %llu bytes of pinned program slots", (unsigned long long)(kSmallSlots * want));
+        return SV_ENOMEM;
+    }
+    h->small_slot_bytes = want;
+    return SV_OK;
+}
+
+// Run the sweeps of gates / groups on a small state: one program, one launch.
+// The step table is read by the kernel from the pinned slot itself (one
+// coalesced read per 192 steps costs less than a copy); a program with large
+// matrices is copied first (reads of 64 KiB over PCIe by one workgroup cost a
+// 12-qubit circuit of 29 blocks more than the copy).  Programs beyond a
+// slot's size go through the arena.
+int run_small(sv_state *h, const std::vector<Block> &gates, const std::vector<Group> &groups, int precision,
+              uint64_t bytes, int ngates, sv_run_stats *st)
+{
+    char *blob = nullptr;
+    const bool in_slot = bytes <= kSmallSlotMax;
+    if (in_slot) {
+        const int rc = ensure_small(h, bytes);
+        if (rc != SV_OK)
+            return rc;
+    }
+    const int slot = h->small_next;
+    if (in_slot) {
+        if (h->small_pending[slot]) {
+            HIP_TRY(hipEventSynchronize(h->small_done[slot]));
+            h->small_pending[slot] = false;
+        }
+        blob = static_cast<char *>(h->h_small) + uint64_t(slot) * h->small_slot_bytes;
+    } else {
+        const int rc = ensure_arena(h, bytes);
+        if (rc != SV_OK)
+            return rc;
+        blob = static_cast<char *>(h->h_arena);
+    }
+    sv_run_stats acc{};
+    acc.gates = ngates;
+    SmallProgram p = small_begin(blob, h->n, h->dtype, groups.size());
+    std::vector<const Block *> mem;
+    Block fused;
+    for (const Group &g : groups) {
+        const Block *b = &gates[size_t(g.members[0])];
+        if (g.members.size() > 1) {
+            mem.clear();
+            for (int m : g.members)
+                mem.push_back(&gates[size_t(m)]);
+            fused = fuse(mem, g.qmask);
+            b = &fused;
+        }
+        int pt[SV_MAX_TARGETS], pc[SV_MAX_CONTROLS];
+        for (int j = 0; j < b->k; ++j)
+            pt[j] = h->qmap[b->targets[j]];
+        for (int j = 0; j < b->c; ++j)
+            pc[j] = h->qmap[b->controls[j]];
+        small_add(p, *b, pt, pc);
+        acc.sweeps += 1;
+        acc.fused_blocks += b->ngates > 1 ? 1 : 0;
+        acc.algorithmic_bytes += block_bytes(h->n, h->dtype, *b, pt, pc);
+        // counted as the launch per sweep counts them: a three-target block
+        // that it pads has the operations of a four-target one
+        acc.flops += padded_exec(h, *b, precision) ? std::ldexp(8.0 * 16.0 - 2.0, h->n - b->c) : block_flops(h->n, *b);
+    }
+    small_end(p);
+    const void *src = blob;
+    if (!in_slot) {
+        const int rc = upload_range(h, 0, bytes);
+        if (rc != SV_OK)
+            return rc;
+        src = h->d_arena;
+    } else if (p.mbuf > 0) {
+        if (!h->d_small && hipMalloc(&h->d_small, kSmallSlots * h->small_slot_bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            h->d_small = nullptr;
+            set_error("cannot allocate device program slots");
+            return SV_ENOMEM;
+        }
+        char *dst = static_cast<char *>(h->d_small) + uint64_t(slot) * h->small_slot_bytes;
+        HIP_TRY(hipMemcpyAsync(dst, blob, bytes, hipMemcpyHostToDevice, h->stream));
+        src = dst;
+    }
+    const hipError_t e = launch_small(h->d_state, p, src, h->stream);
+    if (e != hipSuccess) {
+        set_error("small-state launch failed: %s", hipGetErrorString(e));
+        return SV_EDEVICE;
+    }
+    if (in_slot) {
+        HIP_TRY(hipEventRecord(h->small_done[slot], h->stream));
+        h->small_pending[slot] = true;
+        h->small_next = (slot + 1) % kSmallSlots;
+    } else {
+        HIP_TRY(hipEventRecord(h->arena_done, h->stream));
+        h->arena_pending = true;
+    }
+    if (st)
+        *st = acc;
+    return SV_OK;
+}
+
 // Run a grouped circuit: the blocks are formed, uploaded and launched in
 // chunks of 1, 2, 4, ... blocks, so the host fuses the later blocks while the
 // GPU is already sweeping the earlier ones.  Chunk c's matrices go up in one
@@ -426,6 +591,13 @@ int run_groups(sv_state *h, const std::vector<Block> &gates, const std::vector<G
                int ngates, sv_run_stats *st)
 {
     const size_t nb = groups.size();
+    if (small_route(h, nb, precision)) {
+        uint64_t bytes = 0;
+        for (const Group &g : groups)
+            bytes += small_step_bytes(h->dtype, group_width(gates, g));
+        if (bytes <= kSmallMaxProgram)
+            return run_small(h, gates, groups, precision, bytes, ngates, st);
+    }
     std::vector<uint64_t> offs(nb, 0);
     uint64_t total = 0;
     for (size_t i = 0; i < nb; ++i) {
@@ -836,6 +1008,14 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
 int run_pass_plan(sv_state *h, const std::vector<Block> &gates, const std::vector<PassGroup> &pg, int precision,
                   int ngates, sv_run_stats *st)
 {
+    // without a kernel pass (small states, wide gates) the plan is a sequence
+    // of sweeps
+    if (std::none_of(pg.begin(), pg.end(), [](const PassGroup &w) { return w.kernel; })) {
+        std::vector<Group> groups;
+        for (const PassGroup &w : pg)
+            groups.insert(groups.end(), w.subs.begin(), w.subs.end());
+        return run_groups(h, gates, groups, precision, ngates, st);
+    }
     const uint64_t S = amp_bytes(h->dtype);
     const uint64_t mat16 = (256 * S + 255) & ~uint64_t(255);
     std::vector<PassWork> work(pg.size());
@@ -1114,6 +1294,13 @@ int sv_destroy(sv_handle h)
         (void)hipHostFree(h->h_arena);
     if (h->arena_done)
         (void)hipEventDestroy(h->arena_done);
+    if (h->h_small)
+        (void)hipHostFree(h->h_small);
+    if (h->d_small)
+        (void)hipFree(h->d_small);
+    for (hipEvent_t e : h->small_done)
+        if (e)
+            (void)hipEventDestroy(e);
     for (hipEvent_t e : h->ev_pool)
         (void)hipEventDestroy(e);
     delete h;

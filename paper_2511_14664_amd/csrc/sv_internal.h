@@ -179,6 +179,28 @@ hipError_t launch_dense_bf16x3(void *st, int n, const void *d_U, int k, const in
 bool pads_to_four(int n, int dtype, int c, int precision);
 int dense_path(int n, int dtype, int k, int c, int precision);
 
+// Circuits on small states (sv_small.hip): all sweeps as steps of one launch
+// whose workgroup holds the state in LDS.  The program - step records, then
+// the large matrices - is written to `blob` (host) by small_begin, one
+// small_add per block (pt / pc: physical targets and controls) and small_end,
+// and read by the kernel from `blob` as given to launch_small (the same bytes).
+struct SmallProgram {
+    char *blob;
+    int n, dtype;
+    int count;            // steps added
+    int head;             // first step of the current group of large matrices, -1 if none
+    uint32_t mat;         // offset of the next large matrix
+    uint32_t room;        // LDS bytes for large matrices
+    uint32_t mbuf;        // bytes of the largest group
+};
+bool small_fits(int n, int dtype);
+// Bytes a k-target step takes of a program.
+uint64_t small_step_bytes(int dtype, int k);
+SmallProgram small_begin(char *blob, int n, int dtype, size_t nsteps);
+void small_add(SmallProgram &p, const Block &b, const int *pt, const int *pc);
+void small_end(SmallProgram &p);
+hipError_t launch_small(void *st, const SmallProgram &p, const void *blob, hipStream_t s);
+
 hipError_t launch_bitswap(void *st, int n, int dtype, int lo, int hi, int w, hipStream_t s);
 // dst[j] = amplitude of logical index first + j, j < count.
 hipError_t launch_gather_logical(const void *st, void *dst, int n, int dtype, const int *qmap,

@@ -1938,9 +1938,10 @@ int sv_readout(sv_handle h, const int *qubits, int m, double *probs, const char 
     const bool want_p = probs != nullptr;
     if (!want_p && nterms == 0 && shots == 0)
         return SV_OK;
-    // one read of the state where the marginal's fold route allows it and
-    // every string is a Z string; else the three read-outs one after another
-    if (!z_only || !readout_fusable(h->n, want_p ? m : 0, phys, h->dtype) || (want_p && m == 0)) {
+    // one read of the state where the marginal's fold route allows it; strings
+    // that are not all Z strings, or more than one read-out takes, are read
+    // for themselves; else the three read-outs one after another
+    if (!(want_p || shots > 0 || z_only) || !readout_fusable(h->n, m, phys) || (want_p && m == 0)) {
         if (want_p && (rc = sv_probabilities(h, qubits, m, probs)) != SV_OK)
             return rc;
         if (nterms > 0 && (rc = sv_expect_pauli(h, terms, nterms, expect)) != SV_OK)
@@ -1951,25 +1952,26 @@ int sv_readout(sv_handle h, const int *qubits, int m, double *probs, const char 
     }
     DeviceGuard dg(h->device);
     const int mm = want_p ? m : 0;
-    const int lbs = readout_log_block(h->n, mm, phys, h->dtype);
+    const int nz = z_only ? nterms : 0;  // strings of the fused read
+    const int lbs = readout_log_block(h->n, mm, phys);
     const uint64_t nb = uint64_t(1) << (h->n - lbs);
     const uint64_t nbins = want_p ? uint64_t(1) << m : 0;
-    const uint64_t red = readout_scratch_doubles(h->n, mm, phys, h->dtype);
+    const uint64_t red = readout_scratch_doubles(h->n, mm, phys);
     // scratch: fold and Z partials | block totals | marginal | Z values | shot work
-    const uint64_t need = red + nb + nbins + uint64_t(nterms) + kShotWork * uint64_t(shots);
+    const uint64_t need = red + nb + nbins + uint64_t(nz) + kShotWork * uint64_t(shots);
     rc = ensure_scratch(h, need * 8);
     if (rc != SV_OK)
         return rc;
     // pinned: the uniforms going up; then marginal | Z values | shots coming back
-    const uint64_t nres = nbins + uint64_t(nterms);
+    const uint64_t nres = nbins + uint64_t(nz);
     rc = ensure_pinned(h, (nres + uint64_t(shots)) * 8);
     if (rc != SV_OK)
         return rc;
     double *d_tot = h->d_scratch + red;
     double *d_marg = d_tot + nb;
     double *d_z = d_marg + nbins;
-    double *d_work = d_z + nterms;
-    hipError_t e = launch_readout(h->d_state, h->n, h->dtype, phys, mm, zs.data(), nterms, h->d_scratch,
+    double *d_work = d_z + nz;
+    hipError_t e = launch_readout(h->d_state, h->n, h->dtype, phys, mm, zs.data(), nz, h->d_scratch,
                                   want_p ? d_marg : nullptr, d_z, d_tot, h->stream);
     if (e != hipSuccess) {
         set_error("read-out launch failed: %s", hipGetErrorString(e));
@@ -1987,10 +1989,12 @@ int sv_readout(sv_handle h, const int *qubits, int m, double *probs, const char 
     HIP_TRY(hipStreamSynchronize(h->stream));
     if (want_p)
         memcpy(probs, hp, nbins * 8);
-    if (nterms > 0)
-        memcpy(expect, hp + nbins * 8, uint64_t(nterms) * 8);
+    if (nz > 0)
+        memcpy(expect, hp + nbins * 8, uint64_t(nz) * 8);
     if (shots > 0)
         map_samples(h, reinterpret_cast<const int64_t *>(hp + nres * 8), shots, samples);
+    if (nz < nterms)
+        return sv_expect_pauli(h, terms, nterms, expect);
     return SV_OK;
 }
 

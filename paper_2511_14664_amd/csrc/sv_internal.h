@@ -302,7 +302,7 @@ hipError_t launch_block_sums(const void *st, int n, int dtype, double *d_bsums, 
 // and the shots' uniforms, all on the device (one workgroup).
 hipError_t launch_sample_prep(const double *d_bsums, uint64_t nb, const double *d_uniforms, int shots,
                               int64_t *d_blocks, double *d_targets, hipStream_t s);
-// Per-shot search inside 2^lbs-amplitude blocks (lbs <= 20).
+// Per-shot search inside 2^lbs-amplitude blocks (lbs <= 16).
 hipError_t launch_sample_search(const void *st, int n, int dtype, const int64_t *d_blocks,
                                 const double *d_targets, int shots, int64_t *d_out, int lbs, hipStream_t s);
 // Z strings of one fused read-out.
@@ -310,9 +310,9 @@ constexpr int kReadoutMaxZ = 32;
 // Fused read-out (one read of the state): marginal over phys_q[0..m) (m = 0:
 // none), nt <= 32 Z strings, and the totals of 2^readout_log_block blocks.
 // Possible where readout_fusable; scratch of readout_scratch_doubles.
-bool readout_fusable(int n, int m, const int *phys_q, int dtype);
-int readout_log_block(int n, int m, const int *phys_q, int dtype);
-uint64_t readout_scratch_doubles(int n, int m, const int *phys_q, int dtype);
+bool readout_fusable(int n, int m, const int *phys_q);
+int readout_log_block(int n, int m, const int *phys_q);
+uint64_t readout_scratch_doubles(int n, int m, const int *phys_q);
 hipError_t launch_readout(const void *st, int n, int dtype, const int *phys_q, int m, const uint64_t *zmasks,
                           int nt, double *d_scratch, double *d_marg, double *d_z, double *d_tot, hipStream_t s);
 

@@ -707,54 +707,98 @@ __global__ __launch_bounds__(kThreads) void k_block_sums(const R *__restrict__ s
 
 // Stage 1b (one workgroup): each shot's block and residual target from the
 // block totals, on the device.  Thread c sums the totals of chunk c (nb / 1024
-// consecutive blocks, or one block when nb < 1024) in order; one thread
-// forms the chunks' running sums in order.  Shot s targets t = u_s * norm and
-// takes the first block whose running sum (chunk start + in-chunk partial
-// sum, added in the same order as the chunk total) exceeds t, with residual
-// t minus the running sum before that block.  Running sums are sums of
-// nonnegative terms in one fixed order, so they never decrease and the
-// chunk search and the in-chunk walk agree.  A target at or past the total
-// takes the last block of nonzero total with that total as residual.
+// consecutive blocks, or one block when nb < 1024) in order; running sums over
+// the chunks go in groups of 32: within a group, over the groups, and back.
+// Shot s targets t = u_s * norm and takes the first block whose running sum
+// (chunk start + in-chunk partial sum, added in the same order as the chunk
+// total) exceeds t, with residual t minus the running sum before that block.
+// Every running sum over chunks is a start plus a sum of nonnegative terms in
+// one fixed order, and the next start is that sum at its end, so they never
+// decrease.  Where rounding lets a chunk's walk end just short of the next
+// chunk's start, the shot takes the chunk's last block of nonzero total, and a
+// target at or past the total the last such block of all, each with that total
+// as residual.
+// (One thread adding up all 1024 chunks took most of 47 us at 2^14 blocks.)
 constexpr int kPrepThreads = 1024;
+constexpr int kPrepGroup = 32;
 
 __global__ __launch_bounds__(kPrepThreads) void k_sample_prep(const double *__restrict__ bs, uint64_t nb,
                                                               const double *__restrict__ uni, int shots,
                                                               int64_t *__restrict__ blk, double *__restrict__ tgt)
 {
+    constexpr int NG = kPrepThreads / kPrepGroup;
     __shared__ double csum[kPrepThreads];
     __shared__ double cpre[kPrepThreads + 1];
+    __shared__ double gsum[NG];
+    __shared__ double gpre[NG + 1];
     __shared__ int64_t cnz[kPrepThreads];
+    __shared__ int64_t gnz[NG];
     __shared__ int64_t s_last;
     const int tid = threadIdx.x;
     const uint64_t nchunk = nb < uint64_t(kPrepThreads) ? nb : uint64_t(kPrepThreads);
     const uint64_t cl = nb / nchunk;  // nb is a power of two
-    if (uint64_t(tid) < nchunk) {
+    {
         double acc = 0.0;
         int64_t nz = -1;
-        for (uint64_t b = uint64_t(tid) * cl; b < uint64_t(tid + 1) * cl; ++b) {
-            const double x = bs[b];
-            acc += x;
-            if (x > 0.0)
-                nz = int64_t(b);
+        if (uint64_t(tid) < nchunk) {
+            const double *c = bs + uint64_t(tid) * cl;
+            uint64_t b = 0;
+            for (; b + 8 <= cl; b += 8) {  // eight loads in flight
+                double x[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    x[i] = c[b + i];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    acc += x[i];
+                    nz = x[i] > 0.0 ? int64_t(uint64_t(tid) * cl + b + i) : nz;
+                }
+            }
+            for (; b < cl; ++b) {
+                const double x = c[b];
+                acc += x;
+                nz = x > 0.0 ? int64_t(uint64_t(tid) * cl + b) : nz;
+            }
         }
-        csum[tid] = acc;
+        csum[tid] = acc;  // chunks past the last one: 0
         cnz[tid] = nz;
+    }
+    __syncthreads();
+    if (tid < NG) {
+        double run = 0.0;
+        int64_t last = -1;
+        for (int c = 0; c < kPrepGroup; ++c) {
+            run += csum[tid * kPrepGroup + c];
+            last = cnz[tid * kPrepGroup + c] >= 0 ? cnz[tid * kPrepGroup + c] : last;
+        }
+        gsum[tid] = run;
+        gnz[tid] = last;
     }
     __syncthreads();
     if (tid == 0) {
         double run = 0.0;
         int64_t last = 0;
-        for (uint64_t c = 0; c < nchunk; ++c) {
-            cpre[c] = run;
-            run += csum[c];
-            if (cnz[c] >= 0)
-                last = cnz[c];
+        for (int c = 0; c < NG; ++c) {
+            gpre[c] = run;
+            run += gsum[c];
+            last = gnz[c] >= 0 ? gnz[c] : last;
         }
-        cpre[nchunk] = run;
+        gpre[NG] = run;
         s_last = last;
     }
     __syncthreads();
-    const double norm = cpre[nchunk];
+    if (tid < NG) {
+        const double start = gpre[tid];
+        double part = 0.0;
+        for (int c = 0; c < kPrepGroup; ++c) {
+            cpre[tid * kPrepGroup + c] = start + part;
+            part += csum[tid * kPrepGroup + c];
+        }
+        if (tid == NG - 1)
+            cpre[kPrepThreads] = gpre[NG];
+    }
+    __syncthreads();
+    const double norm = cpre[kPrepThreads];
     for (int sh = tid; sh < shots; sh += kPrepThreads) {
         const double t = uni[sh] * norm;
         uint64_t lo = 0, hi = nchunk;  // first chunk c with cpre[c + 1] > t
@@ -765,18 +809,26 @@ __global__ __launch_bounds__(kPrepThreads) void k_sample_prep(const double *__re
             else
                 lo = mid + 1;
         }
-        int64_t b_out = s_last;
-        double t_out = bs[s_last];
+        int64_t b_out = lo < nchunk ? cnz[lo] : s_last;  // a chunk whose sum moved past t holds a nonzero block
+        double t_out = bs[b_out];
         if (lo < nchunk) {
             const double start = cpre[lo];
             double part = 0.0;
-            for (uint64_t b = lo * cl; b < (lo + 1) * cl; ++b) {
-                const double before = part;
-                part += bs[b];
-                if (start + part > t) {
-                    b_out = int64_t(b);
-                    t_out = t - (start + before);
-                    break;
+            bool hit = false;
+            for (uint64_t b = lo * cl; b < (lo + 1) * cl && !hit; b += 8) {
+                double x[8];  // loads in flight together; past the chunk: 0
+#pragma unroll
+                for (uint64_t i = 0; i < 8; ++i)
+                    x[i] = i < cl ? bs[b + i] : 0.0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const double before = part;
+                    part += x[i];
+                    if (!hit && start + part > t) {
+                        hit = true;
+                        b_out = int64_t(b + i);
+                        t_out = t - (start + before);
+                    }
                 }
             }
         }
@@ -785,10 +837,18 @@ __global__ __launch_bounds__(kPrepThreads) void k_sample_prep(const double *__re
     }
 }
 
-// Stage 2: one workgroup per shot walks its block in segments of 1024
-// amplitudes (4 consecutive per thread) and returns the first index whose
-// in-block running sum exceeds the residual target.  If rounding leaves none,
-// the last index of nonzero probability in the block is returned.
+// Stage 2: one workgroup per shot.  The sums of the block's segments of 1024
+// amplitudes, 4 waves each taking every fourth segment with its loads in
+// flight together, name the segment to start in; from there the block is
+// walked in segments (4 consecutive amplitudes per thread) to the first
+// amplitude of nonzero probability whose in-block running sum exceeds the
+// residual target.  If rounding leaves none, the last index of nonzero
+// probability seen is returned.  (Walking from the block's start, each segment
+// waits for memory: 73 us for 1024 shots in 2^14-amplitude blocks at 28
+// qubits.)
+constexpr int kSearchSegLog = 10;
+constexpr int kSearchMaxLog = 16;
+
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict__ st,
                                                             const int64_t *__restrict__ blocks,
@@ -796,7 +856,10 @@ __global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict_
                                                             int64_t *__restrict__ out, int lbs)
 {
     using C = typename CT<R>::C;
+    constexpr int SEG = 1 << kSearchSegLog;
+    static_assert(SEG == 4 * kThreads, "four amplitudes per thread");
     __shared__ double wsum[4];
+    __shared__ double ssum[1 << (kSearchMaxLog - kSearchSegLog)];
     __shared__ int found;
     __shared__ int lastnz;
     const C *v = reinterpret_cast<const C *>(st);
@@ -809,10 +872,49 @@ __global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict_
         found = 0x7fffffff;
         lastnz = -1;
     }
-    __syncthreads();
     double running = 0.0;
-    for (int seg = 0; seg < bsz; seg += 4 * kThreads) {
-        double c[4];
+    int seg0 = 0;
+    if (bsz > SEG) {
+        const int nseg = bsz >> kSearchSegLog;
+        for (int g = w; g < nseg; g += 8) {
+            const C *va = v + base + (uint64_t(g) << kSearchSegLog);
+            const bool two = g + 4 < nseg;
+            const C *vb = two ? va + 4 * SEG : va;
+            double sa = 0.0, sb = 0.0;
+#pragma unroll
+            for (int k = 0; k < SEG / 64; ++k) {
+                sa += prob(va[k * 64 + lane]);
+                sb += prob(vb[k * 64 + lane]);
+            }
+            sa = wave_sum(sa);
+            sb = wave_sum(sb);
+            if (lane == 0) {
+                ssum[g] = sa;
+                if (two)
+                    ssum[g + 4] = sb;
+            }
+        }
+        __syncthreads();
+        // the first segment whose end passes the target, else the last of
+        // nonzero sum
+        int last = 0;
+        double before = 0.0, lastbefore = 0.0;
+        bool hit = false;
+        for (int g = 0; g < nseg && !hit; ++g) {
+            const double x = ssum[g];
+            if (x > 0.0) {
+                last = g;
+                lastbefore = before;
+            }
+            before += x;
+            hit = before > target;
+        }
+        seg0 = last << kSearchSegLog;
+        running = lastbefore;
+    }
+    __syncthreads();
+    for (int seg = seg0; seg < bsz; seg += SEG) {
+        double c[4], pe[4];
         double acc = 0.0;
         int mynz = -1;
 #pragma unroll
@@ -825,6 +927,7 @@ __global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict_
                 mynz = off;
             acc += p;
             c[e] = acc;
+            pe[e] = p;
         }
         // inclusive scan of thread totals within the wave
         double inc = acc;
@@ -845,7 +948,7 @@ __global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict_
         int cand = 0x7fffffff;
 #pragma unroll
         for (int e = 3; e >= 0; --e)
-            if (excl + c[e] > target && seg + tid * 4 + e < bsz)
+            if (excl + c[e] > target && pe[e] > 0.0)
                 cand = seg + tid * 4 + e;
         if (cand != 0x7fffffff)
             atomicMin(&found, cand);
@@ -865,46 +968,6 @@ __global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict_
         out[s] = int64_t(base + uint64_t(lastnz >= 0 ? lastnz : bsz - 1));
 }
 
-// Two-stage marginal for bins above a high bit: stage 1 sums contiguous
-// segments of 2^s amplitudes (16-byte loads, four independent FP64
-// accumulators per thread, fixed-order tree); stage 2 maps segment sums to
-// bins.  Every amplitude is read exactly once, in address order.
-template <typename R>
-__global__ __launch_bounds__(kThreads) void k_segment_sums(const R *__restrict__ st, double *__restrict__ seg,
-                                                           int s)
-{
-    __shared__ double sh[4];
-    const uint64_t base = uint64_t(blockIdx.x) << s;
-    const uint32_t len = 1u << s;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    if constexpr (std::is_same<R, float>::value) {
-        const float4 *v4 = reinterpret_cast<const float4 *>(st) + (base >> 1);
-        for (uint32_t e = threadIdx.x; e < len / 2; e += 2 * kThreads) {
-            const float4 q = v4[e];
-            a0 += double(q.x) * q.x + double(q.y) * q.y;
-            a1 += double(q.z) * q.z + double(q.w) * q.w;
-            if (e + kThreads < len / 2) {
-                const float4 r = v4[e + kThreads];
-                a2 += double(r.x) * r.x + double(r.y) * r.y;
-                a3 += double(r.z) * r.z + double(r.w) * r.w;
-            }
-        }
-    } else {
-        const double2 *v2 = reinterpret_cast<const double2 *>(st) + base;
-        for (uint32_t e = threadIdx.x; e < len; e += 2 * kThreads) {
-            const double2 q = v2[e];
-            a0 += q.x * q.x + q.y * q.y;
-            if (e + kThreads < len) {
-                const double2 r = v2[e + kThreads];
-                a1 += r.x * r.x + r.y * r.y;
-            }
-        }
-    }
-    const double t = block_sum((a0 + a1) + (a2 + a3), sh);
-    if (threadIdx.x == 0)
-        seg[blockIdx.x] = t;
-}
-
 // out[x] = sum over r of p[dep(x, Q') | ins(r, Q')] on a FP64 array of 2^nb values.
 __global__ __launch_bounds__(kThreads) void k_marg_doubles(const double *__restrict__ p, double *__restrict__ out,
                                                            const MargArgs a)
@@ -920,9 +983,10 @@ __global__ __launch_bounds__(kThreads) void k_marg_doubles(const double *__restr
 }
 
 // ---------------------------------------------------------------------------
-// Marginal, stage 1 for bins with low index bits: fold each 4096-amplitude
-// segment (index bits 0..11) onto its 2^lb bins (the bin bits among bits
-// 0..11), summing 2^F consecutive segments per workgroup.
+// Marginal, stage 1: fold each 4096-amplitude segment (index bits 0..11) onto
+// its 2^lb bins (the bin bits among bits 0..11, none: the segment's sum),
+// summing per workgroup the 2^F segments that F index bits above, not bins,
+// tell apart (foldmask; the lowest such bits).
 // red[(block << lb) | bin] = sum over the workgroup's segments and the
 // segment's non-bin bits.  The probabilities of a segment go to LDS; each
 // bin is summed by G consecutive lanes over interleaved rest indices and
@@ -941,7 +1005,19 @@ struct FoldArgs {
     uint32_t restmask;  // the other segment bits
     int lb;             // popcount(binmask)
     int F;              // log2 segments per workgroup
+    uint64_t foldmask;  // the F index bits that tell them apart
+    Masks outer;        // inserts zeros there
 };
+
+// Index of the first amplitude of segment j of workgroup `block`.
+__device__ __forceinline__ uint64_t fold_base(uint64_t block, uint32_t j, const FoldArgs &a)
+{
+    uint64_t i = insert_zeros(block << kSegLog, a.outer);
+    for (uint64_t m = a.foldmask; j != 0; m &= m - 1, j >>= 1)
+        if (j & 1)
+            i |= m & (~m + 1);
+    return i;
+}
 
 template <typename R>
 constexpr int fold_low_bits()
@@ -965,8 +1041,8 @@ __device__ __forceinline__ uint32_t deposit(uint32_t x, uint32_t mask)
 // the index bits its loads differ in, picks one coefficient per string; the
 // segment's higher bits give a workgroup-uniform sign and the lane's bits a
 // sign applied once at the end), part[t * grid + block]; TOT, the total
-// probability of every 2^tlog consecutive segments, tot[block * 2^(F - tlog)
-// + j].
+// probability of every 2^tlog consecutive segments in index order (the lowest
+// tlog bits of foldmask are bits 12 .. 12 + tlog - 1).
 struct ReadoutArgs {
     uint64_t z[kMaxZ];
     int nt;
@@ -979,7 +1055,6 @@ template <typename R, bool KSUM, int NZ = 0, bool TOT = false>
 __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st, double *__restrict__ red,
                                                         const FoldArgs a, const ReadoutArgs ra)
 {
-    static_assert(NZ == 0 || KSUM, "Z strings ride on the register-summed fold only");
     static_assert(NZ <= kMaxZ && NZ <= 64, "one string per lane");
     constexpr int SEG = 1 << kSegLog;
     constexpr int LOW = fold_low_bits<R>();
@@ -997,6 +1072,7 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
     const int gi = tid % G;
     const int bin0 = tid / G;
     const bool owner_mode = B >= kThreads;
+    const bool one_bin = KSUM && a.lb == 0;  // every bin bit above the segment: threads keep their own sums
     double acc[MAXB];
 #pragma unroll
     for (int k = 0; k < MAXB; ++k)
@@ -1019,7 +1095,7 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
     typedef float f32xL __attribute__((ext_vector_type(F32 ? 4 * NLD : 4)));
     f32xL qn;
     if constexpr (F32) {
-        const float4 *v4 = reinterpret_cast<const float4 *>(st) + ((uint64_t(blockIdx.x) << (a.F + kSegLog)) >> 1);
+        const float4 *v4 = reinterpret_cast<const float4 *>(st) + (fold_base(blockIdx.x, 0, a) >> 1);
 #pragma unroll
         for (int k = 0; k < NLD; ++k) {
             const float4 q = ldnt(&v4[tid + k * kThreads]);
@@ -1027,7 +1103,7 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
         }
     }
     for (uint32_t j = 0; j < (1u << a.F); ++j) {
-        const uint64_t base = ((uint64_t(blockIdx.x) << a.F) | j) << kSegLog;
+        const uint64_t base = fold_base(blockIdx.x, j, a);
         // the thread's 16 probabilities, by the index bits its loads differ in
         // (c64: bit 0 and bits 9..11, as 2 k + c; c128: bits 8..11, as k); a
         // vector value, so that picking a string's coefficient by its
@@ -1036,7 +1112,7 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
         if constexpr (F32) {
             const f32xL qc = qn;
             if (j + 1 < (1u << a.F)) {
-                const float4 *v4 = reinterpret_cast<const float4 *>(st) + ((base + SEG) >> 1);
+                const float4 *v4 = reinterpret_cast<const float4 *>(st) + (fold_base(blockIdx.x, j + 1, a) >> 1);
 #pragma unroll
                 for (int k = 0; k < NLD; ++k) {
                     const float4 q = ldnt(&v4[tid + k * kThreads]);
@@ -1056,6 +1132,8 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
                     const int e = 2 * (tid + k * kThreads);
                     pr[e] = p0;
                     pr[e + 1] = p1;
+                    if constexpr (TOT)
+                        tsum += p0 + p1;
                 }
                 if constexpr (NZ > 0) {
                     w[2 * k] = p0;
@@ -1063,8 +1141,12 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
                 }
             }
             if constexpr (KSUM) {
-                pr[2 * tid] = s0;
-                pr[2 * tid + 1] = s1;
+                if (one_bin) {
+                    acc[0] += s0 + s1;
+                } else {
+                    pr[2 * tid] = s0;
+                    pr[2 * tid + 1] = s1;
+                }
                 if constexpr (TOT)
                     tsum += s0 + s1;
             }
@@ -1075,15 +1157,21 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
             for (int k = 0; k < NLD; ++k) {
                 const double2 q = ldnt(&v2[tid + k * kThreads]);
                 const double p0 = q.x * q.x + q.y * q.y;
-                if constexpr (KSUM)
+                if constexpr (KSUM) {
                     s0 += p0;
-                else
+                } else {
                     pr[tid + k * kThreads] = p0;
+                    if constexpr (TOT)
+                        tsum += p0;
+                }
                 if constexpr (NZ > 0)
                     w[k] = p0;
             }
             if constexpr (KSUM) {
-                pr[tid] = s0;
+                if (one_bin)
+                    acc[0] += s0;
+                else
+                    pr[tid] = s0;
                 if constexpr (TOT)
                     tsum += s0;
             }
@@ -1112,10 +1200,12 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
             if (((j + 1) & ((1u << ra.tlog) - 1)) == 0) {
                 const double tt = block_sum(tsum, sh_tot);
                 if (tid == 0)
-                    ra.tot[(uint64_t(blockIdx.x) << (a.F - ra.tlog)) + (j >> ra.tlog)] = tt;
+                    ra.tot[base >> (kSegLog + ra.tlog)] = tt;
                 tsum = 0.0;
             }
         }
+        if (one_bin)
+            continue;
         __syncthreads();
         if (owner_mode) {
             // bins tid, tid + 256, ...; E <= 16 entries each, ascending
@@ -1147,7 +1237,12 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
         __syncthreads();
     }
     const uint64_t out0 = uint64_t(blockIdx.x) << a.lb;
-    if (owner_mode) {
+    if (one_bin) {
+        __syncthreads();
+        const double all = block_sum(acc[0], pr);
+        if (tid == 0)
+            red[out0] = all;
+    } else if (owner_mode) {
 #pragma unroll
         for (int k = 0; k < MAXB; ++k)
             if (tid + k * kThreads < B)
@@ -1226,44 +1321,58 @@ MargPlan marg_plan(int n, int m)
 
 namespace {
 
-// Route of a marginal: direct (row- or bin-major over the state), segment
-// sums (every bin bit >= 12), or a segment fold (some bin bit < 12) followed
-// by row- or bin-major sums over the folded array.
+// Route of a marginal: direct (row- or bin-major over the state), or a segment
+// fold followed by row- or bin-major sums over the folded array.
 struct MargRoute {
-    int kind;             // 0 direct, 1 segment sums, 2 fold
-    int sb;               // segment bits (kind 1)
-    FoldArgs fold;        // kind 2
-    int n2;               // bits of the folded array (kind 2)
-    std::vector<int> q2;  // bin positions in the folded array (kind 2)
-    MargPlan p2;          // plan over the folded array (kind 2)
-    uint64_t red;         // doubles of the folded / segment array
+    int kind;             // 0 direct, 1 fold
+    FoldArgs fold;        // kind 1
+    int n2;               // bits of the folded array (kind 1)
+    std::vector<int> q2;  // bin positions in the folded array (kind 1)
+    MargPlan p2;          // plan over the folded array (kind 1)
+    uint64_t red;         // doubles of the folded array
     uint64_t scratch;     // doubles of scratch in all
 };
 
-constexpr uint64_t kMaxFolded = uint64_t(1) << 24;  // doubles
+constexpr uint64_t kMaxFolded = uint64_t(1) << 26;  // doubles
+constexpr int kFoldGrid = 12;  // log2 workgroups of a fold, where the bins leave enough bits
 
-// The fold route with 2^F segments per workgroup (the caller checks that
-// bits 12 .. 12 + F - 1 hold no bin and that n >= 14).
-MargRoute fold_route(int n, int m, const int *phys_q, int F)
+// The fold route (n >= kSegLog + 2, at most 10 bins below bit 12): as many
+// fold bits as bring the workgroups down to 2^kFoldGrid, so that their partial
+// sums stay small against the read.
+MargRoute fold_route(int n, int m, const int *phys_q)
 {
     MargRoute r{};
     uint32_t binmask = 0;
-    for (int b = 0; b < m; ++b)
+    uint64_t hibins = 0;
+    for (int b = 0; b < m; ++b) {
         if (phys_q[b] < kSegLog)
             binmask |= 1u << phys_q[b];
+        else
+            hibins |= uint64_t(1) << phys_q[b];
+    }
     const int lb = __builtin_popcount(binmask);
+    std::vector<int> pos;
+    for (int p = kSegLog; p < n && int(pos.size()) < std::min(n - kSegLog - kFoldGrid, n - kSegLog - 1); ++p)
+        if (!((hibins >> p) & 1)) {
+            pos.push_back(p);
+            r.fold.foldmask |= uint64_t(1) << p;
+        }
+    const int F = int(pos.size());
     const int n2 = n - kSegLog - F + lb;
-    r.kind = 2;
+    r.kind = 1;
     r.fold.binmask = binmask;
     r.fold.restmask = ((1u << kSegLog) - 1u) & ~binmask;
     r.fold.lb = lb;
     r.fold.F = F;
+    r.fold.outer = make_masks(pos);
     r.n2 = n2;
     r.red = uint64_t(1) << n2;
     r.q2.resize(size_t(m));
     for (int b = 0; b < m; ++b) {
         const int q = phys_q[b];
-        r.q2[size_t(b)] = q < kSegLog ? __builtin_popcount(binmask & ((1u << q) - 1u)) : lb + q - kSegLog - F;
+        const uint64_t below = (uint64_t(1) << q) - 1;
+        r.q2[size_t(b)] = q < kSegLog ? __builtin_popcount(binmask & uint32_t(below))
+                                      : lb + q - kSegLog - __builtin_popcountll(r.fold.foldmask & below);
     }
     r.p2 = marg_plan(n2, m);
     if (!r.p2.rmajor && m <= 15) {
@@ -1279,35 +1388,15 @@ MargRoute fold_route(int n, int m, const int *phys_q, int F)
 
 MargRoute marg_route(int n, int m, const int *phys_q)
 {
-    MargRoute r{};
-    int b0 = n;
-    uint32_t binmask = 0;
-    uint64_t hibins = 0;
-    for (int b = 0; b < m; ++b) {
-        b0 = std::min(b0, phys_q[b]);
-        if (phys_q[b] < kSegLog)
-            binmask |= 1u << phys_q[b];
-        else
-            hibins |= uint64_t(1) << phys_q[b];
-    }
-    if (n >= kSegLog && b0 >= kSegLog) {
-        r.kind = 1;
-        r.sb = std::min(b0, 16);
-        r.red = uint64_t(1) << (n - r.sb);
-        r.scratch = r.red;
-        return r;
-    }
-    const int lb = __builtin_popcount(binmask);
+    int lb = 0;
+    for (int b = 0; b < m; ++b)
+        lb += phys_q[b] < kSegLog ? 1 : 0;
     if (n >= kSegLog + 2 && lb <= 10) {
-        // fold F more segment bits per workgroup (non-bin bits just above 12)
-        // until the folded array is at most kMaxFolded doubles
-        int F = 0;
-        while (F < n - kSegLog - 1 && !((hibins >> (kSegLog + F)) & 1) &&
-               (uint64_t(1) << (n - kSegLog - F + lb)) > kMaxFolded)
-            ++F;
-        if ((uint64_t(1) << (n - kSegLog - F + lb)) <= 4 * kMaxFolded)
-            return fold_route(n, m, phys_q, F);
+        MargRoute r = fold_route(n, m, phys_q);
+        if (r.red <= kMaxFolded)
+            return r;
     }
+    MargRoute r{};
     const MargPlan p = marg_plan(n, m);
     r.kind = 0;
     r.scratch = p.rmajor ? (uint64_t(1) << m) * p.chunks : 1;
@@ -1328,32 +1417,6 @@ hipError_t launch_marginal(const void *st, int n, int dtype, const int *phys_q, 
         return hipErrorInvalidValue;
     const MargRoute route = marg_route(n, m, phys_q);
     if (route.kind == 1) {
-        const int sb = route.sb;
-        const uint64_t nseg = uint64_t(1) << (n - sb);
-        if (dtype == SV_C64)
-            hipLaunchKernelGGL(k_segment_sums<float>, dim3(uint32_t(nseg)), dim3(kThreads), 0, s, (const float *)st,
-                               d_scratch, sb);
-        else
-            hipLaunchKernelGGL(k_segment_sums<double>, dim3(uint32_t(nseg)), dim3(kThreads), 0, s, (const double *)st,
-                               d_scratch, sb);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-        MargArgs a2{};
-        a2.m = m;
-        a2.rest = uint64_t(1) << (n - sb - m);
-        a2.nbins = uint32_t(1u << m);
-        std::vector<int> q2(phys_q, phys_q + m);
-        for (int b = 0; b < m; ++b) {
-            q2[b] -= sb;
-            a2.qbit[b] = uint64_t(1) << q2[b];
-        }
-        a2.rest_im = make_masks(q2);
-        const uint64_t g = std::min<uint64_t>((uint64_t(a2.nbins) + kThreads - 1) / kThreads, 1u << 20);
-        hipLaunchKernelGGL(k_marg_doubles, dim3(g), dim3(kThreads), 0, s, d_scratch, d_out, a2);
-        return hipGetLastError();
-    }
-    if (route.kind == 2) {
         const uint64_t nblk = uint64_t(1) << (n - kSegLog - route.fold.F);
         if (dtype == SV_C64) {
             if ((route.fold.binmask >> fold_low_bits<float>()) == 0)
@@ -1682,7 +1745,7 @@ hipError_t launch_sample_prep(const double *d_bsums, uint64_t nb, const double *
 hipError_t launch_sample_search(const void *st, int n, int dtype, const int64_t *d_blocks, const double *d_targets,
                                 int shots, int64_t *d_out, int lbs, hipStream_t s)
 {
-    if (shots <= 0 || lbs < 1 || lbs > n || lbs > 20)
+    if (shots <= 0 || lbs < 1 || lbs > n || lbs > kSearchMaxLog)
         return hipSuccess;
     if (dtype == SV_C64)
         hipLaunchKernelGGL(k_sample_search<float>, dim3(shots), dim3(kThreads), 0, s, (const float *)st, d_blocks,
@@ -1703,59 +1766,44 @@ namespace {
 
 // Route of the fused launch; false where the marginal takes another route.
 // m = 0: a fold with no bin bits (the total only).
-// More segments per workgroup than the marginal alone needs: at most 2^12
-// workgroups, so that the per-workgroup reductions of the Z strings (one per
-// string) and the partial sums they leave stay small against the read.
-bool fused_route(int n, int m, const int *phys_q, int dtype, MargRoute &r)
+bool fused_route(int n, int m, const int *phys_q, MargRoute &r)
 {
     if (n < kSegLog + 2)
         return false;
-    int F = 0;
-    uint64_t hibins = 0;
-    if (m > 0) {
-        r = marg_route(n, m, phys_q);
-        if (r.kind != 2)
-            return false;
-        const int low = dtype == SV_C64 ? fold_low_bits<float>() : fold_low_bits<double>();
-        if ((r.fold.binmask >> low) != 0)
-            return false;
-        F = r.fold.F;
-        for (int b = 0; b < m; ++b)
-            if (phys_q[b] >= kSegLog)
-                hibins |= uint64_t(1) << phys_q[b];
-    }
-    const int want = std::max(0, n - kSegLog - 12);
-    while (F < want && F < n - kSegLog - 1 && !((hibins >> (kSegLog + F)) & 1))
-        ++F;
-    while (F < n - kSegLog - 1 && !((hibins >> (kSegLog + F)) & 1) &&
-           (uint64_t(1) << (n - kSegLog - F)) > kMaxFolded)
-        ++F;
-    r = fold_route(n, m, phys_q, F);
-    return true;
+    r = marg_route(n, m, phys_q);
+    return r.kind == 1;
+}
+
+// Consecutive segments whose total one workgroup forms (log2, at most 2).
+int total_log(const FoldArgs &f)
+{
+    if (!((f.foldmask >> kSegLog) & 1))
+        return 0;
+    return ((f.foldmask >> (kSegLog + 1)) & 1) ? 2 : 1;
 }
 
 }  // namespace
 
 static_assert(kMaxZ == kReadoutMaxZ, "Z strings of one fused read-out");
 
-bool readout_fusable(int n, int m, const int *phys_q, int dtype)
+bool readout_fusable(int n, int m, const int *phys_q)
 {
     MargRoute r;
-    return fused_route(n, m, phys_q, dtype, r);
+    return fused_route(n, m, phys_q, r);
 }
 
-int readout_log_block(int n, int m, const int *phys_q, int dtype)
+int readout_log_block(int n, int m, const int *phys_q)
 {
     MargRoute r;
-    if (!fused_route(n, m, phys_q, dtype, r))
+    if (!fused_route(n, m, phys_q, r))
         return -1;
-    return kSegLog + std::min(r.fold.F, 2);
+    return kSegLog + total_log(r.fold);
 }
 
-uint64_t readout_scratch_doubles(int n, int m, const int *phys_q, int dtype)
+uint64_t readout_scratch_doubles(int n, int m, const int *phys_q)
 {
     MargRoute r;
-    if (!fused_route(n, m, phys_q, dtype, r))
+    if (!fused_route(n, m, phys_q, r))
         return 0;
     const uint64_t nblk = uint64_t(1) << (n - kSegLog - r.fold.F);
     return r.scratch + uint64_t(kMaxZ) * nblk;
@@ -1765,29 +1813,36 @@ hipError_t launch_readout(const void *st, int n, int dtype, const int *phys_q, i
                           int nt, double *d_scratch, double *d_marg, double *d_z, double *d_tot, hipStream_t s)
 {
     MargRoute r;
-    if (nt < 0 || nt > kMaxZ || !fused_route(n, m, phys_q, dtype, r))
+    if (nt < 0 || nt > kMaxZ || !fused_route(n, m, phys_q, r))
         return hipErrorInvalidValue;
     const uint64_t nblk = uint64_t(1) << (n - kSegLog - r.fold.F);
     ReadoutArgs ra{};
     ra.nt = nt;
     for (int t = 0; t < nt; ++t)
         ra.z[t] = zmasks[t];
-    ra.tlog = std::min(r.fold.F, 2);
+    ra.tlog = total_log(r.fold);
     ra.zpart = d_scratch + r.scratch;
     ra.tot = d_tot;
     const dim3 g{uint32_t(nblk)}, b{uint32_t(kThreads)};
+    auto launch = [&](auto r_tag, auto ksum_tag) {
+        using R = decltype(r_tag);
+        constexpr bool KSUM = decltype(ksum_tag)::value;
+        const R *p = static_cast<const R *>(st);
+        if (nt > 0)
+            hipLaunchKernelGGL((k_marg_fold<R, KSUM, kMaxZ, true>), g, b, 0, s, p, d_scratch, r.fold, ra);
+        else
+            hipLaunchKernelGGL((k_marg_fold<R, KSUM, 0, true>), g, b, 0, s, p, d_scratch, r.fold, ra);
+    };
     if (dtype == SV_C64) {
-        const float *p = (const float *)st;
-        if (nt > 0)
-            hipLaunchKernelGGL((k_marg_fold<float, true, kMaxZ, true>), g, b, 0, s, p, d_scratch, r.fold, ra);
+        if ((r.fold.binmask >> fold_low_bits<float>()) == 0)
+            launch(float{}, std::true_type{});
         else
-            hipLaunchKernelGGL((k_marg_fold<float, true, 0, true>), g, b, 0, s, p, d_scratch, r.fold, ra);
+            launch(float{}, std::false_type{});
     } else {
-        const double *p = (const double *)st;
-        if (nt > 0)
-            hipLaunchKernelGGL((k_marg_fold<double, true, kMaxZ, true>), g, b, 0, s, p, d_scratch, r.fold, ra);
+        if ((r.fold.binmask >> fold_low_bits<double>()) == 0)
+            launch(double{}, std::true_type{});
         else
-            hipLaunchKernelGGL((k_marg_fold<double, true, 0, true>), g, b, 0, s, p, d_scratch, r.fold, ra);
+            launch(double{}, std::false_type{});
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)

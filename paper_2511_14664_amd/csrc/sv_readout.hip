@@ -99,6 +99,46 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
     return r;
 }
 
+// Sums of v[0 .. C) over the lanes that differ in bits OFF, OFF / 2, .., 1: with
+// each bit a lane keeps the half of the values that its bit names, until one
+// is left.
+template <int C, int OFF, int NT>
+__device__ __forceinline__ void halve_values(double (&v)[NT], int lane)
+{
+    if constexpr (OFF > 0 && C > 1) {
+        const bool hi = (lane & OFF) != 0;
+#pragma unroll
+        for (int i = 0; i < C / 2; ++i) {
+            const double give = hi ? v[i] : v[i + C / 2];
+            v[i] = (hi ? v[i + C / 2] : v[i]) + __shfl_xor(give, OFF, 64);
+        }
+        halve_values<C / 2, OFF / 2>(v, lane);
+    } else if constexpr (OFF > 0) {
+        v[0] += __shfl_xor(v[0], OFF, 64);
+        halve_values<1, OFF / 2>(v, lane);
+    }
+}
+
+// block_sum of NT values at once (a power of two up to 64), the same sums to
+// the bit: each shuffle step hands half of the values still held to the other
+// half of the lanes, 2 NT - 2 shuffles for NT = 32 where one value at a time
+// takes 6 NT.  out(t, sum) is called by one thread for each value.  sh: 4 NT.
+template <int NT, typename F>
+__device__ __forceinline__ void block_sums(double (&v)[NT], double *sh, F out)
+{
+    static_assert(NT >= 1 && NT <= 64 && (NT & (NT - 1)) == 0, "one value per lane");
+    constexpr int LT = __builtin_ctz(NT);
+    const int lane = threadIdx.x & 63;
+    halve_values<NT, 32>(v, lane);
+    __syncthreads();
+    if ((lane & ((64 >> LT) - 1)) == 0)
+        sh[(threadIdx.x >> 6) * NT + (lane >> (6 - LT))] = v[0];
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < NT)
+        out(t, (sh[t] + sh[NT + t]) + (sh[2 * NT + t] + sh[3 * NT + t]));
+}
+
 // ---------------------------------------------------------------------------
 // Marginals.  out[x] = sum over rest index r of |a[dep(x, Q) | ins(r)]|^2.
 // ---------------------------------------------------------------------------
@@ -237,7 +277,7 @@ __global__ __launch_bounds__(kThreads) void k_expect_z(const R *__restrict__ st,
     using C = typename CT<R>::C;
     constexpr int LU = 4, U = 1 << LU;  // amplitudes per thread and step: index bits 8 .. 11
     static_assert(kThreads == 256, "lane and wave bits 0 .. 7");
-    __shared__ double sh[4];
+    __shared__ double sh[4 * NZ];
     const C *v = reinterpret_cast<const C *>(st);
     const int lane = threadIdx.x & 63;
     const uint64_t zl = lane < NZ ? a.z[lane] : 0;  // the string whose parity this lane reports
@@ -281,14 +321,12 @@ __global__ __launch_bounds__(kThreads) void k_expect_z(const R *__restrict__ st,
         }
     }
 #pragma unroll
-    for (int t = 0; t < NZ; ++t) {
-        if (t < a.nt) {
-            const double r = (__popc(threadIdx.x & uint32_t(a.z[t])) & 1) ? -acc[t] : acc[t];
-            const double s = block_sum(r, sh);
-            if (threadIdx.x == 0)
-                part[uint64_t(t) * gridDim.x + blockIdx.x] = s;
-        }
-    }
+    for (int t = 0; t < NZ; ++t)
+        acc[t] = (__popc(threadIdx.x & uint32_t(a.z[t])) & 1) ? -acc[t] : acc[t];
+    block_sums<NZ>(acc, sh, [&](int t, double x) {
+        if (t < a.nt)
+            part[uint64_t(t) * gridDim.x + blockIdx.x] = x;
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -988,16 +1026,20 @@ __global__ __launch_bounds__(kThreads) void k_marg_doubles(const double *__restr
 // summing per workgroup the 2^F segments that F index bits above, not bins,
 // tell apart (foldmask; the lowest such bits).
 // red[(block << lb) | bin] = sum over the workgroup's segments and the
-// segment's non-bin bits.  The probabilities of a segment go to LDS; each
-// bin is summed by G consecutive lanes over interleaved rest indices and
-// combined by a fixed shuffle tree, so the order of every sum is fixed.
+// segment's non-bin bits.  Every thread keeps the sums over the segments of its
+// own 16 amplitudes of a segment in registers; they meet in LDS once, after the
+// last segment, where each bin is summed by G consecutive lanes over
+// interleaved rest indices and combined by a fixed shuffle tree, so the order
+// of every sum is fixed.  (Through LDS with two barriers per segment: 486 us
+// for 9 low bins with 32 Z strings and block totals at 28 qubits c64, 863 us
+// for 10, against 365 and 398.)
 // A thread's loads of one segment differ only in the index bits from
 // fold_low_bits() up: 9..11 for c64 (a 16-byte load holds the two amplitudes
 // of bit 0, the lane gives bits 1..8), 8..11 for c128 (the lane gives bits
-// 0..7).  When none of those bits is a bin bit (KSUM), each
-// thread sums its loads in registers first and the LDS array shrinks to the
-// 2^fold_low_bits() low-bit entries (4 or 2 KiB instead of 32), which leaves room for
-// more resident workgroups to keep loads in flight.
+// 0..7).  When none of those bits is a bin bit (KSUM), one or two sums per
+// thread are enough and the LDS array shrinks to the 2^fold_low_bits() low-bit
+// entries (4 or 2 KiB instead of 32), which leaves room for more resident
+// workgroups to keep loads in flight.
 // ---------------------------------------------------------------------------
 constexpr int kSegLog = 12;
 struct FoldArgs {
@@ -1062,8 +1104,10 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
     constexpr int MAXB = (PR + kThreads - 1) / kThreads;  // bins per thread when every thread owns whole bins
     constexpr bool F32 = std::is_same<R, float>::value;
     constexpr int NLD = F32 ? SEG / (2 * kThreads) : SEG / kThreads;  // loads per thread per segment
+    constexpr int NR = PR / kThreads;  // sums per thread
     __shared__ double pr[PR];
-    __shared__ double sh_tot[TOT || NZ > 0 ? 4 : 1];
+    static_assert(4 * (NZ > 0 ? NZ : 1) <= PR, "the strings' sums reuse pr");
+    __shared__ double sh_tot[TOT ? 4 : 1];
     const int tid = threadIdx.x;
     const uint32_t restmask = KSUM ? (a.restmask & uint32_t(PR - 1)) : a.restmask;
     const int B = 1 << a.lb;
@@ -1072,11 +1116,7 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
     const int gi = tid % G;
     const int bin0 = tid / G;
     const bool owner_mode = B >= kThreads;
-    const bool one_bin = KSUM && a.lb == 0;  // every bin bit above the segment: threads keep their own sums
-    double acc[MAXB];
-#pragma unroll
-    for (int k = 0; k < MAXB; ++k)
-        acc[k] = 0.0;
+    f64x16 own = 0.0;  // NR of them used
     // rest enumeration for the group mode: x_r = deposit(r, restmask), r = gi, gi + G, ...
     const uint32_t x_first = deposit(uint32_t(gi), restmask);
     const uint32_t x_step = deposit(uint32_t(G), restmask);
@@ -1119,63 +1159,39 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
                     qn[4 * k] = q.x, qn[4 * k + 1] = q.y, qn[4 * k + 2] = q.z, qn[4 * k + 3] = q.w;
                 }
             }
-            double s0 = 0.0, s1 = 0.0;
 #pragma unroll
             for (int k = 0; k < NLD; ++k) {
                 const float4 q = make_float4(qc[4 * k], qc[4 * k + 1], qc[4 * k + 2], qc[4 * k + 3]);
                 const double p0 = double(q.x) * q.x + double(q.y) * q.y;
                 const double p1 = double(q.z) * q.z + double(q.w) * q.w;
-                if constexpr (KSUM) {
-                    s0 += p0;
-                    s1 += p1;
-                } else {
-                    const int e = 2 * (tid + k * kThreads);
-                    pr[e] = p0;
-                    pr[e + 1] = p1;
-                    if constexpr (TOT)
-                        tsum += p0 + p1;
-                }
-                if constexpr (NZ > 0) {
-                    w[2 * k] = p0;
-                    w[2 * k + 1] = p1;
-                }
-            }
-            if constexpr (KSUM) {
-                if (one_bin) {
-                    acc[0] += s0 + s1;
-                } else {
-                    pr[2 * tid] = s0;
-                    pr[2 * tid + 1] = s1;
-                }
-                if constexpr (TOT)
-                    tsum += s0 + s1;
+                w[2 * k] = p0;
+                w[2 * k + 1] = p1;
             }
         } else {
             const double2 *v2 = reinterpret_cast<const double2 *>(st) + base;
-            double s0 = 0.0;
 #pragma unroll
             for (int k = 0; k < NLD; ++k) {
                 const double2 q = ldnt(&v2[tid + k * kThreads]);
-                const double p0 = q.x * q.x + q.y * q.y;
-                if constexpr (KSUM) {
-                    s0 += p0;
-                } else {
-                    pr[tid + k * kThreads] = p0;
-                    if constexpr (TOT)
-                        tsum += p0;
-                }
-                if constexpr (NZ > 0)
-                    w[k] = p0;
-            }
-            if constexpr (KSUM) {
-                if (one_bin)
-                    acc[0] += s0;
-                else
-                    pr[tid] = s0;
-                if constexpr (TOT)
-                    tsum += s0;
+                w[k] = q.x * q.x + q.y * q.y;
             }
         }
+        // the thread's own sums over the segments: by load (and by bit 0),
+        // or over the loads where no bin tells them apart
+        double sums[KSUM && F32 ? 2 : 1] = {};
+        if constexpr (KSUM || TOT) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                sums[KSUM && F32 ? k & 1 : 0] += w[k];
+        }
+        if constexpr (KSUM) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+                own[k] += sums[k];
+        } else {
+            own += w;
+        }
+        if constexpr (TOT)
+            tsum += KSUM && F32 ? sums[0] + sums[KSUM && F32 ? 1 : 0] : sums[0];
         if constexpr (NZ > 0) {
             static_assert(NZ == 0 || NLD * (F32 ? 2 : 1) == 16, "16 probabilities per thread and segment");
             // w[k] <- sum_u (-1)^popcount(u & k) p_u
@@ -1204,64 +1220,53 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
                 tsum = 0.0;
             }
         }
-        if (one_bin)
-            continue;
-        __syncthreads();
-        if (owner_mode) {
-            // bins tid, tid + 256, ...; E <= 16 entries each, ascending
-#pragma unroll
-            for (int k = 0; k < MAXB; ++k) {
-                const int bin = tid + k * kThreads;
-                if (bin < B) {
-                    const uint32_t db = deposit(uint32_t(bin), a.binmask);
-                    double sacc = 0.0;
-                    uint32_t x = 0;
-                    for (int r = 0; r < E; ++r) {
-                        sacc += pr[db | x];
-                        x = ((x | ~restmask) + 1u) & restmask;
-                    }
-                    acc[k] += sacc;
-                }
-            }
-        } else if (bin0 < B) {
-            double sacc = 0.0;
-            uint32_t x = x_first;
-            for (int r = gi; r < E; r += G) {
-                sacc += pr[d_bin0 | x];
-                x = ((x | ~restmask) + x_step) & restmask;
-            }
-            for (int off = 1; off < G; off <<= 1)
-                sacc += __shfl_xor(sacc, off, 64);
-            acc[0] += sacc;
-        }
-        __syncthreads();
     }
-    const uint64_t out0 = uint64_t(blockIdx.x) << a.lb;
-    if (one_bin) {
-        __syncthreads();
-        const double all = block_sum(acc[0], pr);
-        if (tid == 0)
-            red[out0] = all;
-    } else if (owner_mode) {
+    // thread tid's own[k] is entry 2 tid + 512 (k / 2) + k % 2 (c64) or
+    // tid + 256 k (c128)
 #pragma unroll
-        for (int k = 0; k < MAXB; ++k)
-            if (tid + k * kThreads < B)
-                red[out0 + tid + k * kThreads] = acc[k];
-    } else if (bin0 < B && gi == 0) {
-        red[out0 + bin0] = acc[0];
+    for (int k = 0; k < NR; ++k)
+        pr[F32 ? 2 * tid + 2 * kThreads * (k >> 1) + (k & 1) : tid + kThreads * k] = own[k];
+    __syncthreads();
+    const uint64_t out0 = uint64_t(blockIdx.x) << a.lb;
+    if (owner_mode) {
+        // bins tid, tid + 256, ...; E <= 16 entries each, ascending
+#pragma unroll
+        for (int k = 0; k < MAXB; ++k) {
+            const int bin = tid + k * kThreads;
+            if (bin < B) {
+                const uint32_t db = deposit(uint32_t(bin), a.binmask);
+                double sacc = 0.0;
+                uint32_t x = 0;
+                for (int r = 0; r < E; ++r) {
+                    sacc += pr[db | x];
+                    x = ((x | ~restmask) + 1u) & restmask;
+                }
+                red[out0 + bin] = sacc;
+            }
+        }
+    } else if (bin0 < B) {
+        double sacc = 0.0;
+        uint32_t x = x_first;
+        for (int r = gi; r < E; r += G) {
+            sacc += pr[d_bin0 | x];
+            x = ((x | ~restmask) + x_step) & restmask;
+        }
+        for (int off = 1; off < G; off <<= 1)
+            sacc += __shfl_xor(sacc, off, 64);
+        if (gi == 0)
+            red[out0 + bin0] = sacc;
     }
     if constexpr (NZ > 0) {
         // the lane's index bits: c64 bits 1..8, c128 bits 0..7
         const uint32_t lbits = F32 ? uint32_t(tid) << 1 : uint32_t(tid);
 #pragma unroll
-        for (int t = 0; t < NZ; ++t) {
-            if (t < ra.nt) {
-                const double r = (__popc(lbits & uint32_t(ra.z[t])) & 1) ? -zacc[t] : zacc[t];
-                const double v = block_sum(r, sh_tot);
-                if (tid == 0)
-                    ra.zpart[uint64_t(t) * gridDim.x + blockIdx.x] = v;
-            }
-        }
+        for (int t = 0; t < NZ; ++t)
+            zacc[t] = (__popc(lbits & uint32_t(ra.z[t])) & 1) ? -zacc[t] : zacc[t];
+        __syncthreads();  // pr is read no more
+        block_sums<NZ>(zacc, pr, [&](int t, double x) {
+            if (t < ra.nt)
+                ra.zpart[uint64_t(t) * gridDim.x + blockIdx.x] = x;
+        });
     }
 }
 

@@ -859,14 +859,14 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
                     used |= 1u << sl;
                 }
             PassSub d{};
-            for (int r = 0; r < 16; ++r)
+            int order[4];  // row bit -> index into slots
+            pass_layout(h->dtype, w.split, T, slots, order, d);
+            int row_of[16];  // row in slots order
+            for (int r = 0; r < 16; ++r) {
+                row_of[r] = 0;
                 for (int j = 0; j < 4; ++j)
-                    if ((r >> j) & 1)
-                        d.xc[r] |= 1u << slots[j];
-            int sorted[4] = {slots[0], slots[1], slots[2], slots[3]};
-            std::sort(sorted, sorted + 4);
-            for (int j = 0; j < 4; ++j)
-                d.tslot_m[j] = (1u << sorted[j]) - 1u;
+                    row_of[r] |= ((r >> j) & 1) << order[j];
+            }
             d.u_off = moff;
             d.nvar = uint32_t(nv);
             for (int j = 0; j < nv; ++j)
@@ -907,7 +907,7 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
                             }
                             int pos = -1;
                             for (int s2 = 0; s2 < 4; ++s2)
-                                if (lq_of_slot[s2] == q)
+                                if (lq_of_slot[order[s2]] == q)
                                     pos = s2;
                             if (pos < 0) {
                                 set_error("pass %zu: phase gate %d outside block %zu", index, m, i);
@@ -943,9 +943,11 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
                 u4.U.assign(256, cd(0.0, 0.0));
                 const int dk = 1 << bv.k;
                 for (int r = 0; r < 16; ++r)
-                    for (int c = 0; c < 16; ++c)
-                        if ((r >> bv.k) == (c >> bv.k))
-                            u4.U[size_t(r) * 16 + c] = bv.U[size_t(r & (dk - 1)) * dk + (c & (dk - 1))];
+                    for (int c = 0; c < 16; ++c) {
+                        const int ro = row_of[r], co = row_of[c];
+                        if ((ro >> bv.k) == (co >> bv.k))
+                            u4.U[size_t(r) * 16 + c] = bv.U[size_t(ro & (dk - 1)) * dk + (co & (dk - 1))];
+                    }
                 if (w.presplit)
                     pass_presplit(u4.U.data(), static_cast<char *>(h->h_arena) + d.u_off + var * mat16);
                 else

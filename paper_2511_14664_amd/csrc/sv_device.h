@@ -86,12 +86,18 @@ __device__ __forceinline__ uint32_t swz(uint32_t x)
     return x ^ ((x >> 6) & 63u);
 }
 
-// The same without touching bit 0 (bits 7..11 into bits 1..5): an amplitude
-// pair (2m, 2m + 1) stays adjacent and in order, so a tile sweep moves it as
-// one 16-byte LDS access.  Also linear over XOR and its own inverse.
-__device__ __forceinline__ uint32_t swz_p(uint32_t x)
+// Swizzle of a pass tile: every index bit above the bank bits (16 slots of 16
+// bytes, 32 of 8) is folded onto one of them, so that a block whose lanes take
+// almost any tile bits can reach all banks with each access (pass_layout picks
+// the lanes' bits).  Complex64 leaves bit 0 alone: an amplitude pair
+// (2m, 2m + 1) stays adjacent and in order, and a tile sweep moves it as one
+// 16-byte LDS access.  Linear over XOR and its own inverse, for tiles of up to
+// 13 (complex64) and 12 bits.
+template <typename R>
+__host__ __device__ __forceinline__ uint32_t swz_p(uint32_t x)
 {
-    return x ^ ((x >> 6) & 62u);
+    return std::is_same<R, float>::value ? x ^ ((x >> 4) & 30u) ^ ((x >> 8) & 30u)
+                                         : x ^ ((x >> 4) & 15u) ^ ((x >> 8) & 15u);
 }
 
 // Geometry of one LDS tile: the amplitudes spanned by the k target bits and
@@ -222,8 +228,11 @@ __device__ __forceinline__ void st_nt(float4 *p, float4 v)
 // blockIdx.x, see tile_grid) so that no workgroup loops: a loop would let the
 // compiler hoist the per-tile constants into registers.  PAIR (complex64
 // with physical bit 0 inside the tile) moves amplitude pairs as 16-byte
-// accesses.  NTH is the workgroup size (256 or 512 threads); REMAT
-// recomputes the store addresses after compute() instead of keeping them;
+// accesses.  NTH is the workgroup size (256 or 512 threads).  An address is a
+// wave-uniform part (the tile's base, the wave's bits and the access number's)
+// plus the offset of the lane's six bits, computed once: one vector add per
+// access (with every thread bit deposited per access the sweeps' 2 x 134
+// vector instructions per wave were a fifth of a four-block pass's).
 // PSWZ lays the tile out with swz_p (pairs as 16-byte LDS accesses; the
 // tile must then be 16-byte aligned and compute() must use swz_p).
 //
@@ -237,7 +246,7 @@ struct SameSlot {
     __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return x; }
 };
 
-template <typename R, int TA_LOG, bool PAIR, int NTH = kThreads, bool REMAT = false, bool PSWZ = false, typename F,
+template <typename R, int TA_LOG, bool PAIR, int NTH = kThreads, bool PSWZ = false, typename F,
           typename S = SameSlot>
 __device__ __forceinline__ void tile_sweep(R *__restrict__ st, const TileArgs &a, typename CT<R>::C *tile,
                                            F &&compute, S src = S())
@@ -251,98 +260,86 @@ __device__ __forceinline__ void tile_sweep(R *__restrict__ st, const TileArgs &a
     static_assert(!PAIR || std::is_same<R, float>::value, "16-byte pairs are complex64 only");
     constexpr int LO = PAIR ? 1 : 0;  // tile bits below the thread bits
     const int tid = threadIdx.x;
-    uint64_t off_lo = 0;
-#pragma unroll
-    for (int b = 0; b < TB; ++b)
-        if ((tid >> b) & 1)
-            off_lo |= a.dep[b + LO];
-    auto offset = [&](int s) -> uint64_t {
-        uint64_t off = off_lo;
-#pragma unroll
-        for (int b = TB + LO; b < TA_LOG; ++b)
-            if ((s >> (b - TB - LO)) & 1)
-                off |= a.dep[b];
-        return off;
-    };
     const uint64_t o = uint64_t(blockIdx.y) * gridDim.x + blockIdx.x;
     if (o >= a.ntiles)
         return;
-    const uint64_t base = insert_zeros(o, a.outer) | a.cmask;
-    {
-        if constexpr (PAIR) {
-            const float4 *v4 = reinterpret_cast<const float4 *>(st);
-            float4 q[OPT / 2];
+    const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(tid >> 6));
+    uint64_t base = insert_zeros(o, a.outer) | a.cmask;
 #pragma unroll
-            for (int s = 0; s < OPT / 2; ++s)
-                q[s] = ld_nt(&v4[(base + offset(s)) >> 1]);
+    for (int b = 6; b < TB; ++b)
+        base |= a.dep[b + LO] & (0 - uint64_t((wave >> (b - 6)) & 1));
+    uint64_t lane_off = 0;  // bytes
 #pragma unroll
-            for (int s = 0; s < OPT / 2; ++s) {
-                const uint32_t x = 2u * uint32_t(s * NTH + tid);
-                if constexpr (PSWZ) {
-                    *reinterpret_cast<float4 *>(&tile[swz_p(x)]) = q[s];
-                } else {
-                    tile[swz(x)] = make_float2(q[s].x, q[s].y);
-                    tile[swz(x + 1)] = make_float2(q[s].z, q[s].w);
-                }
-            }
-        } else {
-            const C *v = reinterpret_cast<const C *>(st);
-            R qr[OPT], qi[OPT];  // scalar arrays: vector-typed ones go to scratch
+    for (int b = 0; b < 6; ++b)
+        lane_off |= (a.dep[b + LO] * sizeof(C)) & (0 - uint64_t((tid >> b) & 1));
+    // uniform pointer of access s
+    auto at = [&](int s) -> char * {
+        uint64_t i = base;
 #pragma unroll
-            for (int s = 0; s < OPT; ++s) {
-                const C q = ld_nt(&v[base + offset(s)]);
-                qr[s] = q.x;
-                qi[s] = q.y;
-            }
+        for (int b = TB + LO; b < TA_LOG; ++b)
+            if ((s >> (b - TB - LO)) & 1)
+                i |= a.dep[b];
+        return reinterpret_cast<char *>(st) + i * sizeof(C);
+    };
+    if constexpr (PAIR) {
+        float4 q[OPT / 2];
 #pragma unroll
-            for (int s = 0; s < OPT; ++s) {
-                C q;
-                q.x = qr[s];
-                q.y = qi[s];
-                tile[PSWZ ? swz_p(uint32_t(s * NTH + tid)) : swz(uint32_t(s * NTH + tid))] = q;
+        for (int s = 0; s < OPT / 2; ++s)
+            q[s] = ld_nt(reinterpret_cast<const float4 *>(at(s) + lane_off));
+#pragma unroll
+        for (int s = 0; s < OPT / 2; ++s) {
+            const uint32_t x = 2u * uint32_t(tid);
+            if constexpr (PSWZ) {
+                *reinterpret_cast<float4 *>(&tile[swz_p<R>(x) ^ swz_p<R>(2u * uint32_t(s * NTH))]) = q[s];
+            } else {
+                const uint32_t y = 2u * uint32_t(s * NTH) + x;
+                tile[swz(y)] = make_float2(q[s].x, q[s].y);
+                tile[swz(y + 1)] = make_float2(q[s].z, q[s].w);
             }
         }
-        __syncthreads();
-        compute(tile);
-        // REMAT: the store addresses are recomputed from a copy of the thread
-        // index the compiler cannot see through (an empty asm), so they are
-        // not held in registers, or spilled, across a register-hungry
-        // compute().
-        int tid2 = tid;
-        if constexpr (REMAT)
-            asm volatile("" : "+v"(tid2));
-        uint64_t off_lo2 = 0;
+    } else {
+        R qr[OPT], qi[OPT];  // scalar arrays: vector-typed ones go to scratch
 #pragma unroll
-        for (int b = 0; b < TB; ++b)
-            if ((tid2 >> b) & 1)
-                off_lo2 |= a.dep[b + LO];
-        auto offset2 = [&](int s) -> uint64_t {
-            uint64_t off = off_lo2;
-#pragma unroll
-            for (int b = TB + LO; b < TA_LOG; ++b)
-                if ((s >> (b - TB - LO)) & 1)
-                    off |= a.dep[b];
-            return off;
-        };
-        if constexpr (PAIR) {
-            float4 *v4 = reinterpret_cast<float4 *>(st);
-#pragma unroll
-            for (int s = 0; s < OPT / 2; ++s) {
-                const uint32_t x = 2u * uint32_t(s * NTH + tid2);
-                if constexpr (PSWZ) {
-                    st_nt(&v4[(base + offset2(s)) >> 1], *reinterpret_cast<const float4 *>(&tile[swz_p(x)]));
-                } else {
-                    const C lo = tile[swz(src(x))], hi = tile[swz(src(x + 1))];
-                    st_nt(&v4[(base + offset2(s)) >> 1], make_float4(lo.x, lo.y, hi.x, hi.y));
-                }
-            }
-        } else {
-            C *v = reinterpret_cast<C *>(st);
-#pragma unroll
-            for (int s = 0; s < OPT; ++s)
-                st_nt(&v[base + offset2(s)],
-                      tile[PSWZ ? swz_p(uint32_t(s * NTH + tid2)) : swz(src(uint32_t(s * NTH + tid2)))]);
+        for (int s = 0; s < OPT; ++s) {
+            const C q = ld_nt(reinterpret_cast<const C *>(at(s) + lane_off));
+            qr[s] = q.x;
+            qi[s] = q.y;
         }
+#pragma unroll
+        for (int s = 0; s < OPT; ++s) {
+            C q;
+            q.x = qr[s];
+            q.y = qi[s];
+            tile[PSWZ ? swz_p<R>(uint32_t(tid)) ^ swz_p<R>(uint32_t(s * NTH)) : swz(uint32_t(s * NTH + tid))] = q;
+        }
+    }
+    __syncthreads();
+    compute(tile);
+    // an empty asm the compiler cannot see through: the per-access addresses
+    // are formed again rather than held in registers, or spilled, across a
+    // register-hungry compute()
+    int tid2 = tid;
+    asm volatile("" : "+v"(lane_off), "+v"(tid2));
+    if constexpr (PAIR) {
+#pragma unroll
+        for (int s = 0; s < OPT / 2; ++s) {
+            const uint32_t x = 2u * uint32_t(tid2);
+            float4 *p = reinterpret_cast<float4 *>(at(s) + lane_off);
+            if constexpr (PSWZ) {
+                st_nt(p, *reinterpret_cast<const float4 *>(
+                             &tile[swz_p<R>(x) ^ swz_p<R>(2u * uint32_t(s * NTH))]));
+            } else {
+                const uint32_t y = 2u * uint32_t(s * NTH) + x;
+                const C lo = tile[swz(src(y))], hi = tile[swz(src(y + 1))];
+                st_nt(p, make_float4(lo.x, lo.y, hi.x, hi.y));
+            }
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < OPT; ++s)
+            st_nt(reinterpret_cast<C *>(at(s) + lane_off),
+                  tile[PSWZ ? swz_p<R>(uint32_t(tid2)) ^ swz_p<R>(uint32_t(s * NTH))
+                            : swz(src(uint32_t(s * NTH + tid2)))]);
     }
 }
 

@@ -216,29 +216,32 @@ uint64_t expect_scratch_doubles(int n);
 // one tile of the pass's qubits + the lowest free bits.
 constexpr int kMaxPassQubits = 8;
 struct PassSub {
-    uint32_t xc[16];      // tile-local index bits of block row r (bit b of r -> slot of block qubit b)
-    uint32_t tslot_m[4];  // insert masks 2^slot - 1 of the block's four slots, ascending
+    uint32_t rx[4];       // LDS byte offset (XOR-linear, swizzled) of bit b of a block row
+    uint32_t gx[9];       // of bit b of a group index: lanes take bits 0..3, waves and their items the rest
     uint64_t u_off;       // byte offset of the 16 x 16 row-major matrix (state precision) from the matrix base
     uint64_t t_off;       // byte offset of the block's phase terms (PassTerm) from the matrix base
     uint32_t nterm;       // number of phase terms (0: the matrix alone)
     uint32_t nvar;        // matrix variants 2^nvar, selected by the tile's index bits vpos[0..nvar)
     uint8_t vpos[8];
     uint32_t pslot;       // with nterm > 0: this block's row of the per-tile angle table (< kMaxTermBlocks)
-    uint32_t pad0b;
-    uint64_t pad;
+    uint32_t pad;
 };
+// Lay out a block on the tile slots slots[0..4): order[b] is the index into
+// slots of row bit b, chosen with the lanes' group bits so that the kernel's
+// LDS accesses spread over all banks where the slots allow it; fills d.rx, d.gx.
+void pass_layout(int dtype, bool split, int T, const int *slots, int *order, PassSub &d);
 // Blocks carrying phase terms per pass (rows of the kernel's per-tile angle
 // table in LDS); a pass with more runs as ordinary sweeps.
 constexpr int kMaxTermBlocks = 16;
 // A split-BF16 pass block without phase terms carries its 16 x 16 matrix
-// already split: per lane of the MFMA wave, 3 parts x (real, imaginary
-// output rows) x 4 packed BF16 pairs (pass_presplit).
+// already split: per lane of the MFMA wave, 3 parts x 2 output tiles x 4
+// packed BF16 pairs (pass_presplit).
 constexpr uint64_t kPresplitBytes = 3 * 2 * 64 * 16;
 // Write the split A fragments of the 16 x 16 complex matrix U (row-major,
 // FP64, rounded to FP32 first) to dst (kPresplitBytes): the same exact
 // three-part BF16 split that the pass kernel applies to per-tile matrices.
 void pass_presplit(const std::complex<double> *U, void *dst);
-static_assert(sizeof(PassSub) == 128, "pass block descriptor layout");
+static_assert(sizeof(PassSub) == 96, "pass block descriptor layout");
 // One monomial of a per-tile phase: where the tile's outer index bits cover
 // omask (physical bits), entry (r, c) of the block matrix gains the angle
 // 2 pi turn / 2^64 if the block-local column index c (front) or row index r

@@ -31,6 +31,7 @@
 // phases are folded into the block's matrix as a column phase (applied before
 // the block) or a row phase (after it), from a list of monomials (outer-bit
 // mask, slot mask, angle) per block evaluated once per tile into LDS.
+#include <algorithm>
 #include <cstring>
 
 #include "sv_device.h"
@@ -106,6 +107,16 @@ __device__ __forceinline__ void turn_sincos(uint64_t u, double &sn, double &cs)
         cs = -cs;
 }
 
+// XOR of x[b] over the set bits b < n of v.
+__device__ __forceinline__ uint32_t lane_bits(int v, const uint32_t *x, int n)
+{
+    uint32_t r = 0;
+#pragma unroll
+    for (int b = 0; b < n; ++b)
+        r ^= x[b] & uint32_t(-((v >> b) & 1));
+    return r;
+}
+
 // Integer add to an LDS word (wrapping).
 __device__ __forceinline__ void lds_add(uint32_t *p, uint32_t v)
 {
@@ -133,7 +144,8 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
     constexpr int NW = NTH / 64;  // waves
     constexpr int PER_WAVE = NGS / NW;
     constexpr bool F64 = std::is_same<R, double>::value;
-    static_assert(NGS % NW == 0 && PER_WAVE >= 1, "tile shape");
+    constexpr int LG = TA_LOG - 8;  // group bits above the lanes'
+    static_assert(NGS % NW == 0 && PER_WAVE >= 1 && LG <= 5, "tile shape");
 
     __shared__ __align__(16) C tile[1 << TA_LOG];
     const int tid = threadIdx.x;
@@ -219,7 +231,7 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
         }
     };
 
-    tile_sweep<R, TA_LOG, PAIR, NTH, true, true>(st, a, tile, [&](C *t) {
+    tile_sweep<R, TA_LOG, PAIR, NTH, true>(st, a, tile, [&](C *t) {
         if (PHASES) {
             fill_angles();
             __syncthreads();
@@ -232,33 +244,20 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
             if (sb + 1 < nsub)
                 load_u(sb + 1, nr, ni);
             const PassSub &d = subs[sb];
-            // LDS addresses.  The slot deposit of a group index and the XOR
-            // swizzle are both linear over XOR, and the index splits into
-            // disjoint lane bits (row bits from bkk or the accumulator row,
-            // group bits 0..3 from bj) and wave-uniform bits (row bits from
-            // the k-step or register, group bits from wave + NW j): the lane
-            // parts are computed once per block, the uniform parts on the
-            // scalar unit, and each access costs one XOR.
-            const uint32_t x1 = d.xc[1], x2 = d.xc[2], x4 = d.xc[4], x8 = d.xc[8];
-            const uint32_t xb_lane = ((bkk & 1) ? x1 : 0u) | ((bkk & 2) ? x2 : 0u);
-            const uint32_t xo_lane = F64 ? (((q & 1) ? x1 : 0u) | ((q & 2) ? x2 : 0u))
-                                         : (((q & 1) ? x4 : 0u) | ((q & 2) ? x8 : 0u));
-            auto deposit = [&](uint32_t g) {
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint32_t lo = d.tslot_m[b];
-                    g = (g & lo) | ((g & ~lo) << 1);
-                }
-                return g;
-            };
-            // byte offsets into the tile (the XOR parts scale with it)
-            constexpr int SH = F64 ? 4 : 3;
-            const uint32_t gl = deposit(uint32_t(bj));
-            const uint32_t in_lane = swz_p(xb_lane | gl) << SH, out_lane = swz_p(xo_lane | gl) << SH;
+            // LDS addresses.  The byte offset of a (row, group) is linear over
+            // XOR in its bits (d.rx, d.gx: swizzled), and the bits are the
+            // lane's (row bits from bkk or the accumulator row, group bits
+            // 0..3 from bj) or wave-uniform (row bits from the k-step or
+            // register, group bits from wave + NW j): the lane parts are
+            // computed once per block, the uniform parts on the scalar unit,
+            // and each access costs one XOR.
+            const uint32_t gl = lane_bits(bj, d.gx, 4);
+            const uint32_t in_lane = gl ^ lane_bits(bkk, d.rx, 2);
+            const uint32_t out_lane = F64 ? in_lane : gl ^ lane_bits(q, d.rx + 2, 2);
             uint32_t hj[PER_WAVE];
 #pragma unroll
             for (int j = 0; j < PER_WAVE; ++j)
-                hj[j] = swz_p(deposit(uint32_t(wave + NW * j) * NT)) << SH;
+                hj[j] = lane_bits(wave + NW * j, d.gx + 4, LG);
             char *tb = reinterpret_cast<char *>(t);
             AccT p1[PER_WAVE], p2[PER_WAVE], p3[PER_WAVE];
 #pragma unroll
@@ -269,7 +268,7 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
             }
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                const uint32_t ss = swz_p(d.xc[s * KT]) << SH;
+                const uint32_t ss = lane_bits(s, d.rx + 2, 2);
                 const R us = ur[s] + ui[s];
 #pragma unroll
                 for (int j = 0; j < PER_WAVE; ++j) {
@@ -285,7 +284,7 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 // accumulator row: 4 (lane / 16) + r (FP32), 4 r + lane / 16 (FP64)
-                const uint32_t rr = swz_p(d.xc[F64 ? 4 * r : r]) << SH;
+                const uint32_t rr = lane_bits(r, d.rx + (F64 ? 2 : 0), 2);
 #pragma unroll
                 for (int j = 0; j < PER_WAVE; ++j) {
                     C y;
@@ -324,10 +323,15 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
 //
 // The K index is ordered so that lane l (q = l / 16, j = l % 16) supplies
 // B[8 q + 2 r + c][j] = component c of amplitude row 4 q + r of group j, and
-// receives D[4 q + r][j]: each lane reads and writes the same four
-// amplitudes of a group, so a block needs no barrier between group sets.
-// Its A fragment A[j][8 q + 2 r + c] holds U entries of row j, column
-// 4 q + r.  Products are accumulated smallest first.
+// receives D[4 q + i][j]: output tile t holds component i % 2 of row
+// 4 q + 2 t + i / 2 there, so each lane reads and writes the same four
+// amplitudes of a group (no barrier between group sets) and each amplitude's
+// components come out in two adjacent registers, as the LDS write takes them.
+// A[j][8 q + 2 r + c] of tile t holds U entries of row 4 (j / 4) + 2 t +
+// j % 4 / 2, column 4 q + r.  Products are accumulated smallest first.
+//
+// Vector instructions bound the kernel (a wave's 12 matrix products of a
+// group set take 192 cycles, 69 vector instructions 276): XXX
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -370,6 +374,13 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t &h, uint32_t &
     m = pack_bf16(ra, rb);
     const float sa = minus_lo(ra, m), sb = minus_hi(rb, m);
     l = pack_bf16(sa, sb);
+}
+
+// x of another lane of the lane's four: SEL holds two bits per lane.
+template <int SEL>
+__device__ __forceinline__ float quad_move(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), SEL, 0xf, 0xf, true));
 }
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(const uint32_t *w)
@@ -441,8 +452,8 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
         ui[3] = u1.w;
     };
     // otherwise: this lane's split A fragments of block sb, in the order
-    // (h, real rows), (h, imaginary rows), (m, real), (m, imag), (l, real),
-    // (l, imag), four registers each
+    // (h, tile 0), (h, tile 1), (m, 0), (m, 1), (l, 0), (l, 1), four registers
+    // each
     auto load_a = [&](int sb, uint32_t *A) {
         const PassSub &d = subs[sb];
         const uint4 *P = reinterpret_cast<const uint4 *>(mats + d.u_off + size_t(variant(d)) * kPresplitBytes) + lane;
@@ -456,11 +467,11 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
         }
     };
     float ur[4], ui[4];
-    uint32_t an[PHASES ? 1 : 24];
+    uint32_t a0[24], a1[24];  // this block's and the next one's
     if constexpr (PHASES)
         load_u(0, ur, ui);  // in flight with the tile's loads
     else
-        load_a(0, an);
+        load_a(0, a0);
 
     // per-tile phase angles, as in k_pass (fixed-point turns, 32 bits)
     __shared__ uint32_t angles[PHASES ? kMaxTermBlocks * 32 : 1];
@@ -490,84 +501,99 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
         }
     };
 
-    tile_sweep<float, TA_LOG, true, NTH, true, true>(st, a, tile, [&](C *t) {
+    tile_sweep<float, TA_LOG, true, NTH, true>(st, a, tile, [&](C *t) {
         if (PHASES) {
             fill_angles();
             __syncthreads();
         }
-        for (int sb = 0; sb < nsub; ++sb) {
+        // A operands of block sb from its FP32 fragment, this tile's phases
+        // applied
+        auto split_u = [&](int sb, uint32_t *A) {
             const PassSub &d = subs[sb];
-            // A operands: real rows [Ur, -Ui], imaginary rows [Ui, Ur], split
-            uint32_t A[24];
-            if constexpr (PHASES) {
-                if (d.nterm > 0) {
-                    // U[r][c] exp(i (front(c) + back(r))), r = j16, c = 4 q + k
-                    const uint32_t *row = angles + d.pslot * 32;
-                    const uint32_t tb = row[16 + j16];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        float sn, cs;
-                        turn_sincos(uint32_t(row[4 * q + k] + tb), sn, cs);
-                        const float r0 = ur[k], i0 = ui[k];
-                        ur[k] = r0 * cs - i0 * sn;
-                        ui[k] = r0 * sn + i0 * cs;
-                    }
-                }
+            if (d.nterm > 0) {
+                // U[r][c] exp(i (front(c) + back(r))), r = j16, c = 4 q + k
+                const uint32_t *row = angles + d.pslot * 32;
+                const uint32_t tb = row[16 + j16];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    split3(ur[k], -ui[k], A[k], A[8 + k], A[16 + k]);
-                    split3(ui[k], ur[k], A[4 + k], A[12 + k], A[20 + k]);
+                    float sn, cs;
+                    turn_sincos(uint32_t(row[4 * q + k] + tb), sn, cs);
+                    const float r0 = ur[k], i0 = ui[k];
+                    ur[k] = r0 * cs - i0 * sn;
+                    ui[k] = r0 * sn + i0 * cs;
                 }
-                if (sb + 1 < nsub)
-                    load_u(sb + 1, ur, ui);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 24; ++i)
-                    A[i] = an[i];
-                if (sb + 1 < nsub)
-                    load_a(sb + 1, an);
             }
-            const uint32_t *arh = A, *aih = A + 4, *arm = A + 8, *aim = A + 12, *arl = A + 16, *ail = A + 20;
-            // LDS byte offsets (XOR-linear parts, as in k_pass): lane part
-            // from (q, j16), register part from the row r, wave-uniform part
-            // from the group set
-            const uint32_t x4 = d.xc[4], x8 = d.xc[8];
-            auto deposit = [&](uint32_t g) {
+            // output tile t takes row 2 t + j16 % 4 / 2 of the lane's four:
+            // real rows [Ur, -Ui], imaginary rows [Ui, Ur]
+            const bool im = (lane & 1) != 0;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint32_t lo = d.tslot_m[b];
-                    g = (g & lo) | ((g & ~lo) << 1);
-                }
-                return g;
-            };
-            const uint32_t lane_off = swz_p(((q & 1) ? x4 : 0u) | ((q & 2) ? x8 : 0u) | deposit(uint32_t(j16))) << 3;
-            uint32_t roff[4];
+            for (int k = 0; k < 4; ++k) {
+                const float r0 = quad_move<0x50>(ur[k]), i0 = quad_move<0x50>(ui[k]);
+                const float r1 = quad_move<0xfa>(ur[k]), i1 = quad_move<0xfa>(ui[k]);
+                split3(im ? i0 : r0, im ? r0 : -i0, A[k], A[8 + k], A[16 + k]);
+                split3(im ? i1 : r1, im ? r1 : -i1, A[4 + k], A[12 + k], A[20 + k]);
+            }
+        };
+        // LDS byte offsets (XOR-linear parts, as in k_pass): lane part from
+        // (q, j16), register part from the row r, wave-uniform part from the
+        // group set
+        char *tb = reinterpret_cast<char *>(t);
+        auto block = [&](int sb, const uint32_t *A) {
+            const PassSub &d = subs[sb];
+            const uint32_t lane_off = lane_bits(j16, d.gx, 4) ^ lane_bits(q, d.rx + 2, 2);
+            uint32_t uoff[PER_WAVE][4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                roff[r] = swz_p(d.xc[r]) << 3;
-            char *tb = reinterpret_cast<char *>(t);
+            for (int g = 0; g < PER_WAVE; ++g)
 #pragma unroll
-            for (int g = 0; g < PER_WAVE; ++g) {
-                const uint32_t hoff = swz_p(deposit(uint32_t(wave + NW * g) * NT)) << 3;
-                float v[8];
+                for (int r = 0; r < 4; ++r)
+                    uoff[g][r] = lane_bits(wave + NW * g, d.gx + 4, 4) ^ lane_bits(r, d.rx, 2);
+            float v[8];
+            auto read = [&](int g) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const C x = *reinterpret_cast<const C *>(tb + (lane_off ^ (roff[r] ^ hoff)));
+                    const C x = *reinterpret_cast<const C *>(tb + (lane_off ^ uoff[g][r]));
                     v[2 * r] = x.x;
                     v[2 * r + 1] = x.y;
                 }
+            };
+            read(0);
+#pragma unroll
+            for (int g = 0; g < PER_WAVE; ++g) {
                 uint32_t bh[4], bm[4], bl[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     split3(v[2 * r], v[2 * r + 1], bh[r], bm[r], bl[r]);
+                if (g + 1 < PER_WAVE)
+                    read(g + 1);  // other groups than the ones written below
                 const bf16x8_t Bh = as_bf16x8(bh), Bm = as_bf16x8(bm), Bl = as_bf16x8(bl);
-                const floatx4 yr = mma_split6(arh, arm, arl, Bh, Bm, Bl);
-                const floatx4 yi = mma_split6(aih, aim, ail, Bh, Bm, Bl);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    *reinterpret_cast<C *>(tb + (lane_off ^ (roff[r] ^ hoff))) = make_float2(yr[r], yi[r]);
+                const floatx4 y0 = mma_split6(A, A + 8, A + 16, Bh, Bm, Bl);
+                const floatx4 y1 = mma_split6(A + 4, A + 12, A + 20, Bh, Bm, Bl);
+                *reinterpret_cast<C *>(tb + (lane_off ^ uoff[g][0])) = make_float2(y0[0], y0[1]);
+                *reinterpret_cast<C *>(tb + (lane_off ^ uoff[g][1])) = make_float2(y0[2], y0[3]);
+                *reinterpret_cast<C *>(tb + (lane_off ^ uoff[g][2])) = make_float2(y1[0], y1[1]);
+                *reinterpret_cast<C *>(tb + (lane_off ^ uoff[g][3])) = make_float2(y1[2], y1[3]);
             }
             __syncthreads();
+        };
+        if constexpr (PHASES) {
+            for (int sb = 0; sb < nsub; ++sb) {
+                split_u(sb, a0);
+                if (sb + 1 < nsub)
+                    load_u(sb + 1, ur, ui);
+                block(sb, a0);
+            }
+        } else {
+            // two blocks per iteration, each loading the other's operands
+            for (int sb = 0; sb < nsub; sb += 2) {
+                if (sb + 1 < nsub)
+                    load_a(sb + 1, a1);
+                block(sb, a0);
+                if (sb + 1 < nsub) {
+                    if (sb + 2 < nsub)
+                        load_a(sb + 2, a0);
+                    block(sb + 1, a1);
+                }
+            }
         }
     });
 }
@@ -627,17 +653,74 @@ void pass_presplit(const std::complex<double> *U, void *dst)
     uint32_t *o = static_cast<uint32_t *>(dst);
     for (int lane = 0; lane < 64; ++lane) {
         const int q = lane / 16, j = lane % 16;
-        for (int k = 0; k < 4; ++k) {
-            const std::complex<double> u = U[j * 16 + 4 * q + k];
-            const float re = float(u.real()), im = float(u.imag());
-            uint32_t p[2][3];
-            split3_host(re, -im, p[0][0], p[0][1], p[0][2]);
-            split3_host(im, re, p[1][0], p[1][1], p[1][2]);
-            for (int part = 0; part < 3; ++part)
-                for (int rt = 0; rt < 2; ++rt)
-                    o[((part * 2 + rt) * 64 + lane) * 4 + k] = p[rt][part];
-        }
+        for (int t = 0; t < 2; ++t)
+            for (int k = 0; k < 4; ++k) {
+                const std::complex<double> u = U[(4 * (j / 4) + 2 * t + j % 4 / 2) * 16 + 4 * q + k];
+                const float re = float(u.real()), im = float(u.imag());
+                uint32_t p[3];
+                if (j % 2 == 0)
+                    split3_host(re, -im, p[0], p[1], p[2]);
+                else
+                    split3_host(im, re, p[0], p[1], p[2]);
+                for (int part = 0; part < 3; ++part)
+                    o[((part * 2 + t) * 64 + lane) * 4 + k] = p[part];
+            }
     }
+}
+
+// Bank bit that tile bit b reaches under swz_p, -1 for none: complex64 accesses
+// are 8 bytes wide and half a wave's cover 32 slots (bits 0..4), complex128 ones
+// 16 bytes and a quarter wave's cover 16 (bits 0..3).
+static int bank_bit(int dtype, int b)
+{
+    const uint32_t y = dtype == SV_C64 ? swz_p<float>(1u << b) : swz_p<double>(1u << b);
+    const uint32_t m = y & (dtype == SV_C64 ? 31u : 15u);
+    return m ? __builtin_ctz(m) : -1;
+}
+
+// The lanes that one access serves together differ in the four group bits and,
+// complex64, in the low lane row bit (row bit 2 of the split kernel, whose lanes
+// take row bits 2 and 3, 0 of the others).  Each should reach a bank bit of its
+// own: the row bit takes one that no group bit reaches, if there is one.
+// (Group bits in ascending order and the swizzle x ^ (x >> 6): two thirds of
+// the LDS cycles of a 29-qubit QFT's low passes were conflicts.)
+void pass_layout(int dtype, bool split, int T, const int *slots, int *order, PassSub &d)
+{
+    const bool f32 = dtype == SV_C64;
+    const int nbank = f32 ? 5 : 4;
+    auto off = [&](int b) { return f32 ? swz_p<float>(1u << b) << 3 : swz_p<double>(1u << b) << 4; };
+    uint32_t used = 0;
+    for (int j = 0; j < 4; ++j)
+        used |= 1u << slots[j];
+    int by_bank[5] = {-1, -1, -1, -1, -1};  // lowest group bit reaching each bank bit
+    for (int b = T - 1; b >= 0; --b)
+        if (!((used >> b) & 1) && bank_bit(dtype, b) >= 0)
+            by_bank[bank_bit(dtype, b)] = b;
+    int row = 0, row_bank = -1;  // the slot of the lanes' low row bit
+    if (f32)
+        for (int j = 0; j < 4; ++j) {
+            const int k = bank_bit(dtype, slots[j]);
+            if (k >= 0 && (row_bank < 0 || (by_bank[k] < 0 && by_bank[row_bank] >= 0))) {
+                row = j;
+                row_bank = k;
+            }
+        }
+    int g[9], n = 0;
+    for (int k = 0; k < nbank && n < 4; ++k)
+        if (k != row_bank && by_bank[k] >= 0) {
+            g[n++] = by_bank[k];
+            used |= 1u << by_bank[k];
+        }
+    for (int b = 0; b < T; ++b)
+        if (!((used >> b) & 1))
+            g[n++] = b;
+    for (int b = 0; b < T - 4; ++b)
+        d.gx[b] = off(g[b]);
+    for (int b = 0; b < 4; ++b)
+        order[b] = b;
+    std::swap(order[split ? 2 : 0], order[row]);
+    for (int b = 0; b < 4; ++b)
+        d.rx[b] = off(slots[order[b]]);
 }
 
 int pass_tile_log(int dtype)

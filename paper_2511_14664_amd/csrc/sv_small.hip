@@ -134,7 +134,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
     const uint32_t tid = threadIdx.x;
     const uint32_t wave = uni(tid >> 6), lane = tid & 63;
     auto at = [&](uint32_t off) __attribute__((always_inline)) -> C & { return *reinterpret_cast<C *>(tile + off); };
-    auto slot = [](uint32_t x) __attribute__((always_inline)) { return swz_p(x) * uint32_t(sizeof(C)); };
+    // bits 7..11 folded onto bits 1..5: linear over XOR, pairs stay adjacent
+    auto slot = [](uint32_t x) __attribute__((always_inline)) { return (x ^ ((x >> 6) & 62u)) * uint32_t(sizeof(C)); };
 
     const uint32_t nvec = uint32_t(sizeof(C) << n) / 16;
     constexpr uint32_t PERV = 16 / sizeof(C);  // amplitudes per 16-byte vector
@@ -526,7 +527,7 @@ void small_add(SmallProgram &p, const Block &b, const int *pt, const int *pc)
         g.lo = bits - 1;
         g.ctl = fixed;
         const uint32_t amp = p.dtype == SV_C64 ? 8 : 16;
-        g.pt = (bits ^ ((bits >> 6) & 62u)) * amp;  // swz_p
+        g.pt = (bits ^ ((bits >> 6) & 62u)) * amp;  // the kernel's slot()
         const uint32_t flags = !b.diag ? 0 : b.U[0] == cd(1.0, 0.0) ? kGateDiag | kGateKeep : kGateDiag;
         g.kind = kStepGate | flags << 8 | 1u << 16;
         std::memcpy(rec, &g, sizeof g);

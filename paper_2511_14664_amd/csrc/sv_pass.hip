@@ -396,7 +396,7 @@ __device__ __forceinline__ floatx4 mma_split6(const uint32_t *ah, const uint32_t
 // FP32 and every workgroup applies its tile's phases and splits them.
 // Otherwise the matrices come split already (pass_presplit), and the kernel
 // only loads each lane's A fragments.  NTH: 256 threads (five workgroups per
-// CU, for passes of several blocks) or 512 (three, for one-block passes,
+// CU, for passes of several blocks) or 512 (three, for one-block passes only,
 // which are bound by HBM: 8 waves share a tile's loads and its one block).
 template <bool PHASES, int NTH>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NTH == 256 ? (PHASES ? 4 : 5) : 1)))
@@ -570,6 +570,8 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
                     load_u(sb + 1, ur, ui);
                 block(sb, a0);
             }
+        } else if constexpr (NTH == 512) {
+            block(0, a0);  // one-block passes only: no second operand set
         } else {
             // two blocks per iteration, each loading the other's operands
             for (int sb = 0; sb < nsub; sb += 2) {

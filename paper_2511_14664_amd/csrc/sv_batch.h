@@ -38,7 +38,29 @@ struct BPass {
     int32_t last;                    // last pass: reduce expectation values instead of storing
     uint32_t mat0;                   // first matrix element of the pass's steps
     uint32_t nmat;                   // matrix elements of the pass's steps, contiguous from mat0
+    int32_t run0;                    // register runs covering the pass's steps (none: one sweep per step)
+    int32_t nruns;
 };
+
+// Register runs: consecutive steps (in an order that keeps every qubit's) that
+// act on at most lp - kBatchThreadLog tile bits.  Each thread holds the
+// amplitudes over those bits in registers, and the tile moves through LDS once
+// per run instead of once per step.  Tiles of 2^11 amplitudes and more, where a
+// thread holds at least kRunMinBits bits.
+constexpr int kRunMinBits = 3;
+constexpr int kRunMaxBits = 5;
+constexpr bool batch_runs(int lp)
+{
+    return lp >= kBatchThreadLog + kRunMinBits && lp <= kBatchThreadLog + kRunMaxBits;
+}
+struct BRun {
+    int32_t step0;
+    int32_t nsteps;
+    uint8_t reg[kRunMaxBits];      // tile bits of the register index's bits
+    uint8_t lane[kBatchThreadLog]; // tile bits of the thread index's bits
+    uint8_t pad[3];
+};
+static_assert(sizeof(BRun) == 24, "run record layout");
 
 // Per-pass copies in LDS, taken at the start of every task: the first
 // kBatchStepCache steps, and every matrix when they fit in
@@ -46,9 +68,10 @@ struct BPass {
 constexpr int kBatchStepCache = 128;
 constexpr int kBatchMatCacheBytes = 8192;
 
-// One in-LDS gate step.  type 0: dense one-qubit on tile bit a; 1: one-qubit
-// on tile bit a controlled by tile bit b; 2: dense two-qubit, matrix index bit
-// 0 on tile bit a and bit 1 on tile bit b.
+// One gate step.  type 0: dense one-qubit on tile bit a; 1: one-qubit on tile
+// bit a controlled by tile bit b; 2: dense two-qubit, matrix index bit 0 on
+// tile bit a and bit 1 on tile bit b.  In a register run a and b are bits of
+// the register index, and a < b for type 2.
 struct BStep {
     uint32_t mat;  // offset of the matrix in complex elements
     uint8_t type;
@@ -77,6 +100,7 @@ struct BatchArgs {
     const BInst *inst;
     const BPass *pass;
     const BStep *steps;
+    const BRun *runs;
     const void *mats;
     const BTask *tasks;
     const uint64_t *zmasks;
@@ -92,6 +116,6 @@ struct BatchArgs {
 hipError_t launch_batch(int dtype, const BatchArgs &a, uint32_t grid, size_t lds, hipStream_t s);
 hipError_t launch_batch_fill(uint32_t *ctr, uint32_t n, hipStream_t s);
 // Persistent grid for the batch kernel with `lds` dynamic bytes per workgroup.
-uint32_t batch_grid(int dtype, size_t lds);
+uint32_t batch_grid(int dtype, int tile_log, size_t lds);
 
 }  // namespace sv

@@ -33,6 +33,7 @@ struct StepPlan {
     uint64_t qmask;
     uint32_t mat;              // complex offset in the matrix buffer
     int d;                     // matrix dimension
+    bool swap;                 // two-qubit: the step's index bits are the block's in reverse
 };
 
 template <typename T>
@@ -80,6 +81,7 @@ struct sv_batch {
     BInst *d_inst = nullptr;
     BPass *d_pass = nullptr;
     BStep *d_steps = nullptr;
+    BRun *d_runs = nullptr;
     BTask *d_tasks = nullptr;
     uint64_t *d_z = nullptr;
     double *d_part = nullptr;
@@ -108,7 +110,7 @@ void free_build(sv_batch *b)
         (void)hipGraphDestroy(b->graph);
     b->exec = nullptr;
     b->graph = nullptr;
-    void *bufs[] = {b->d_states, b->d_inst, b->d_pass, b->d_steps, b->d_tasks, b->d_z, b->d_part, b->d_out,
+    void *bufs[] = {b->d_states, b->d_inst, b->d_pass, b->d_steps, b->d_runs, b->d_tasks, b->d_z, b->d_part, b->d_out,
                     b->d_ctr, b->d_mats};
     for (void *p : bufs)
         if (p)
@@ -117,6 +119,7 @@ void free_build(sv_batch *b)
     b->d_inst = nullptr;
     b->d_pass = nullptr;
     b->d_steps = nullptr;
+    b->d_runs = nullptr;
     b->d_tasks = nullptr;
     b->d_z = nullptr;
     b->d_part = nullptr;
@@ -231,17 +234,24 @@ void fill_matrices(sv_batch *b)
                     mem.push_back(&blocks[size_t(m)]);
                 const Block f = fuse(mem, sp.qmask);
                 const size_t dd = size_t(sp.d) * sp.d;
+                // entry (r, c) with both qubits exchanged: 0 1 2 3 -> 0 2 1 3
+                auto from = [&](size_t e) {
+                    auto x = [](size_t v) { return (v & 1) << 1 | v >> 1; };
+                    return sp.swap ? x(e >> 2) << 2 | x(e & 3) : e;
+                };
                 if (b->dtype == SV_C64) {
                     float *dst = static_cast<float *>(b->h_mats) + 2 * size_t(sp.mat);
                     for (size_t e = 0; e < dd; ++e) {
-                        dst[2 * e] = float(f.U[e].real());
-                        dst[2 * e + 1] = float(f.U[e].imag());
+                        const cd &u = f.U[from(e)];
+                        dst[2 * e] = float(u.real());
+                        dst[2 * e + 1] = float(u.imag());
                     }
                 } else {
                     double *dst = static_cast<double *>(b->h_mats) + 2 * size_t(sp.mat);
                     for (size_t e = 0; e < dd; ++e) {
-                        dst[2 * e] = f.U[e].real();
-                        dst[2 * e + 1] = f.U[e].imag();
+                        const cd &u = f.U[from(e)];
+                        dst[2 * e] = u.real();
+                        dst[2 * e + 1] = u.imag();
                     }
                 }
             }
@@ -256,6 +266,78 @@ void fill_matrices(sv_batch *b)
         t.join();
 }
 
+// Cut a pass's steps into register runs (sv_batch.h): each run takes, in
+// order, every remaining step whose tile bits fit with those already taken and
+// that no step left behind shares a bit with, so each tile bit sees its steps
+// in their order.  Reorders steps and plans alike and rewrites the steps' bits
+// as register bits.
+void cut_runs(int lp, std::vector<BStep> &steps, std::vector<StepPlan> &plans, size_t first,
+              std::vector<BRun> &runs)
+{
+    const int nr = lp - kBatchThreadLog;
+    auto bits_of = [](const BStep &s) { return 1u << s.a | (s.type != 0 ? 1u << s.b : 0u); };
+    std::vector<BStep> left(steps.begin() + ptrdiff_t(first), steps.end());
+    std::vector<StepPlan> pleft(plans.begin() + ptrdiff_t(first), plans.end());
+    steps.resize(first);
+    plans.erase(plans.begin() + ptrdiff_t(first), plans.end());
+    while (!left.empty()) {
+        uint32_t set = 0, blocked = 0;
+        BRun run{};
+        run.step0 = int32_t(steps.size());
+        std::vector<BStep> rest;
+        std::vector<StepPlan> prest;
+        for (size_t k = 0; k < left.size(); ++k) {
+            const uint32_t m = bits_of(left[k]);
+            if ((m & blocked) == 0 && __builtin_popcount(set | m) <= nr) {
+                set |= m;
+                steps.push_back(left[k]);
+                plans.push_back(pleft[k]);
+            } else {
+                blocked |= m;
+                rest.push_back(left[k]);
+                prest.push_back(pleft[k]);
+            }
+        }
+        for (int x = 0; x < lp && __builtin_popcount(set) < nr; ++x)
+            set |= 1u << x;
+        int bit_of[kBatchMaxTileLog], n = 0;
+        for (int x = 0; x < lp; ++x)
+            if ((set >> x) & 1) {
+                bit_of[x] = n;
+                run.reg[n++] = uint8_t(x);
+            }
+        // the lanes that LDS serves together (the lowest thread bits) on tile
+        // bits of different banks: the kernel's swizzle puts tile bit x < 12 on
+        // bank bit x % 6
+        uint32_t lanes = 0;
+        n = 0;
+        for (int c = 0; c < 5; ++c)
+            for (int x = c; x < lp && x < 12; x += 6)
+                if (!((set >> x) & 1)) {
+                    run.lane[n++] = uint8_t(x);
+                    lanes |= 1u << x;
+                    break;
+                }
+        for (int x = 0; x < lp; ++x)
+            if (!(((set | lanes) >> x) & 1))
+                run.lane[n++] = uint8_t(x);
+        run.nsteps = int32_t(steps.size()) - run.step0;
+        for (int k = run.step0; k < run.step0 + run.nsteps; ++k) {
+            BStep &s = steps[size_t(k)];
+            s.a = uint8_t(bit_of[s.a]);
+            if (s.type != 0)
+                s.b = uint8_t(bit_of[s.b]);
+            if (s.type == 2 && s.a > s.b) {
+                std::swap(s.a, s.b);
+                plans[size_t(k)].swap = true;
+            }
+        }
+        runs.push_back(run);
+        left.swap(rest);
+        pleft.swap(prest);
+    }
+}
+
 int build(sv_batch *b)
 {
     free_build(b);
@@ -264,6 +346,7 @@ int build(sv_batch *b)
     std::vector<BInst> inst(b->ninst);
     std::vector<BPass> passes;
     std::vector<BStep> steps;
+    std::vector<BRun> runs;
     std::vector<uint64_t> zs;
     b->steps.clear();
     uint64_t state_off = 0;
@@ -315,7 +398,7 @@ int build(sv_batch *b)
             for (int k : pp[p].gates)
                 pg.push_back(g[k]);
             for (const Group &gr : group_greedy(pg, fw)) {
-                StepPlan sp;
+                StepPlan sp{};
                 sp.inst = i;
                 for (int m : gr.members)
                     sp.members.push_back(pp[p].gates[m]);
@@ -341,11 +424,16 @@ int build(sv_batch *b)
                     return SV_EUNSUPPORTED;
                 }
                 sp.d = 1 << f.k;
-                sp.mat = mat;
-                st.mat = mat;
-                mat += uint32_t(sp.d * sp.d);
                 steps.push_back(st);
                 b->steps.push_back(sp);
+            }
+            bp.run0 = int32_t(runs.size());
+            if (batch_runs(bp.lp))
+                cut_runs(bp.lp, steps, b->steps, size_t(bp.step0), runs);
+            bp.nruns = int32_t(runs.size()) - bp.run0;
+            for (size_t k = size_t(bp.step0); k < steps.size(); ++k) {
+                steps[k].mat = b->steps[k].mat = mat;
+                mat += uint32_t(b->steps[k].d * b->steps[k].d);
             }
             bp.nsteps = int(steps.size()) - bp.step0;
             bp.mat0 = bp.nsteps > 0 ? steps[size_t(bp.step0)].mat : mat;
@@ -355,6 +443,7 @@ int build(sv_batch *b)
         ntiles_of[i].assign(pp.size(), nt);
     }
     b->mat_elems = mat;
+    steps.push_back(BStep{});  // a run's last step reads the record after it
     b->total_terms = out_off;
     // tasks: level-major (pass p of every circuit before pass p+1), widest first
     std::vector<int> order(b->ninst);
@@ -377,7 +466,7 @@ int build(sv_batch *b)
         return SV_ENOMEM;
     }
     if ((rc = dev_upload(b->d_inst, inst, s)) != SV_OK || (rc = dev_upload(b->d_pass, passes, s)) != SV_OK ||
-        (rc = dev_upload(b->d_steps, steps, s)) != SV_OK || (rc = dev_upload(b->d_tasks, tasks, s)) != SV_OK ||
+        (rc = dev_upload(b->d_steps, steps, s)) != SV_OK || (rc = dev_upload(b->d_runs, runs, s)) != SV_OK || (rc = dev_upload(b->d_tasks, tasks, s)) != SV_OK ||
         (rc = dev_upload(b->d_z, zs, s)) != SV_OK)
         return rc;
     std::vector<double> zero_part(std::max(1, part_off), 0.0);
@@ -390,7 +479,8 @@ int build(sv_batch *b)
     std::vector<uint32_t> zc(b->nctr, 0u);
     if ((rc = dev_upload(b->d_ctr, zc, s)) != SV_OK)
         return rc;
-    const size_t mat_bytes = std::max<size_t>(1, b->mat_elems) * 2 * (S / 2);
+    // padded: a matrix is read as 16 elements whatever its size
+    const size_t mat_bytes = (b->mat_elems + 16) * S;
     if (hipMalloc(&b->d_mats, mat_bytes) != hipSuccess ||
         hipHostMalloc(&b->h_mats, mat_bytes, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&b->h_out, std::max(1, out_off) * sizeof(double), hipHostMallocDefault) != hipSuccess ||
@@ -404,13 +494,14 @@ int build(sv_batch *b)
         return SV_EDEVICE;
     }
     b->lds = batch_lds_bytes(L, S);
-    b->grid = batch_grid(b->dtype, b->lds);
+    b->grid = batch_grid(b->dtype, L, b->lds);
 
     BatchArgs a{};
     a.states = b->d_states;
     a.inst = b->d_inst;
     a.pass = b->d_pass;
     a.steps = b->d_steps;
+    a.runs = b->d_runs;
     a.mats = b->d_mats;
     a.tasks = b->d_tasks;
     a.zmasks = b->d_z;

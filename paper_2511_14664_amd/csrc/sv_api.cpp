@@ -870,7 +870,7 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
             d.u_off = moff;
             d.nvar = uint32_t(nv);
             for (int j = 0; j < nv; ++j)
-                d.vpos[j] = uint8_t(h->qmap[vql[j]]);
+                d.vpos |= uint64_t(h->qmap[vql[j]]) << (8 * j);
             moff += (uint64_t(1) << nv) * mat16;
             // phase terms: (physical outer mask, block-local slot mask, side)
             d.t_off = terms + nt * sizeof(PassTerm);

@@ -52,6 +52,20 @@ __host__ __device__ __forceinline__ uint64_t insert_zeros(uint64_t g, const Inse
     return g;
 }
 
+// The same with im.n = N known: the masks come in a few wide scalar loads
+// instead of one load and wait each.
+template <int N>
+__device__ __forceinline__ uint64_t insert_zeros_n(uint64_t g, const InsertMasks &im)
+{
+    static_assert(N <= kMaxIns, "masks");
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const uint64_t lo = im.m[j];
+        g = (g & lo) | ((g & ~lo) << 1);
+    }
+    return g;
+}
+
 template <typename C>
 __device__ __forceinline__ C cmad(C u, C v, C acc)
 {
@@ -240,16 +254,20 @@ __device__ __forceinline__ void st_nt(float4 *p, float4 v)
 // must leave its results in the same LDS slots and end with __syncthreads().
 // src(x) (identity by default) is the tile-local index whose LDS slot the
 // store of element x reads: a permutation of the tile applied on the way out
-// (not with PSWZ).
+// (not with PSWZ).  loads() is called once the tile's loads are issued: what
+// compute() needs first, in flight behind them.
 // ---------------------------------------------------------------------------
 struct SameSlot {
     __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return x; }
 };
+struct NoLoads {
+    __device__ __forceinline__ void operator()() const {}
+};
 
 template <typename R, int TA_LOG, bool PAIR, int NTH = kThreads, bool PSWZ = false, typename F,
-          typename S = SameSlot>
+          typename S = SameSlot, typename L = NoLoads>
 __device__ __forceinline__ void tile_sweep(R *__restrict__ st, const TileArgs &a, typename CT<R>::C *tile,
-                                           F &&compute, S src = S())
+                                           F &&compute, S src = S(), L loads = L())
 {
     using C = typename CT<R>::C;
     constexpr int TA = 1 << TA_LOG;
@@ -264,7 +282,8 @@ __device__ __forceinline__ void tile_sweep(R *__restrict__ st, const TileArgs &a
     if (o >= a.ntiles)
         return;
     const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(tid >> 6));
-    uint64_t base = insert_zeros(o, a.outer) | a.cmask;
+    // a pass tile (PSWZ) has no controls: its outer mask is the tile's bits
+    uint64_t base = PSWZ ? insert_zeros_n<TA_LOG>(o, a.outer) : insert_zeros(o, a.outer) | a.cmask;
 #pragma unroll
     for (int b = 6; b < TB; ++b)
         base |= a.dep[b + LO] & (0 - uint64_t((wave >> (b - 6)) & 1));
@@ -286,6 +305,13 @@ __device__ __forceinline__ void tile_sweep(R *__restrict__ st, const TileArgs &a
 #pragma unroll
         for (int s = 0; s < OPT / 2; ++s)
             q[s] = ld_nt(reinterpret_cast<const float4 *>(at(s) + lane_off));
+        if constexpr (!std::is_same<L, NoLoads>::value) {
+            // (the fences keep the tile's loads, these, and the waits for
+            // the tile in this order)
+            asm volatile("" ::: "memory");
+            loads();
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int s = 0; s < OPT / 2; ++s) {
             const uint32_t x = 2u * uint32_t(tid);
@@ -304,6 +330,13 @@ __device__ __forceinline__ void tile_sweep(R *__restrict__ st, const TileArgs &a
             const C q = ld_nt(reinterpret_cast<const C *>(at(s) + lane_off));
             qr[s] = q.x;
             qi[s] = q.y;
+        }
+        if constexpr (!std::is_same<L, NoLoads>::value) {
+            // (the fences keep the tile's loads, these, and the waits for
+            // the tile in this order)
+            asm volatile("" ::: "memory");
+            loads();
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int s = 0; s < OPT; ++s) {

@@ -221,8 +221,8 @@ struct PassSub {
     uint64_t u_off;       // byte offset of the 16 x 16 row-major matrix (state precision) from the matrix base
     uint64_t t_off;       // byte offset of the block's phase terms (PassTerm) from the matrix base
     uint32_t nterm;       // number of phase terms (0: the matrix alone)
-    uint32_t nvar;        // matrix variants 2^nvar, selected by the tile's index bits vpos[0..nvar)
-    uint8_t vpos[8];
+    uint32_t nvar;        // matrix variants 2^nvar, selected by the tile's index bits vpos
+    uint64_t vpos;        // byte j: position of bit j of the variant number
     uint32_t pslot;       // with nterm > 0: this block's row of the per-tile angle table (< kMaxTermBlocks)
     uint32_t pad;
 };

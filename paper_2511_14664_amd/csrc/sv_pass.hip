@@ -117,6 +117,16 @@ __device__ __forceinline__ uint32_t lane_bits(int v, const uint32_t *x, int n)
     return r;
 }
 
+// Number of a block's matrix variant on the tile at tbase (scalar unit: read
+// through byte loads its latency stood before every tile's and block's loads).
+__device__ __forceinline__ uint32_t variant_of(uint64_t tbase, const PassSub &d)
+{
+    uint32_t var = 0;
+    for (uint32_t j = 0; j < d.nvar; ++j)
+        var |= uint32_t((tbase >> ((d.vpos >> (8 * j)) & 63)) & 1) << j;
+    return var;
+}
+
 // Integer add to an LDS word (wrapping).
 __device__ __forceinline__ void lds_add(uint32_t *p, uint32_t v)
 {
@@ -156,15 +166,13 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
     const int q = lane / 16;
 
     // this tile's index bits outside the tile (variant selection, phase terms)
-    const uint64_t tbase = insert_zeros(uint64_t(blockIdx.y) * gridDim.x + blockIdx.x, a.outer);
+    const uint64_t tbase = insert_zeros_n<TA_LOG>(uint64_t(blockIdx.y) * gridDim.x + blockIdx.x, a.outer);
     // this lane's fragment of block sb's matrix: U[ai][4 s + akk], s < NS;
     // a block with variants stores one matrix per value of its selecting
     // index bits, consecutively
     auto load_u = [&](int sb, R *xr, R *xi) {
         const PassSub &d = subs[sb];
-        uint32_t var = 0;
-        for (uint32_t j = 0; j < d.nvar; ++j)
-            var |= uint32_t((tbase >> d.vpos[j]) & 1) << j;
+        const uint32_t var = variant_of(tbase, d);
         const C *U = reinterpret_cast<const C *>(mats + d.u_off) + size_t(var) * (D * D) + ai * D + akk;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
@@ -174,7 +182,6 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
         }
     };
     R ur[NS], ui[NS];
-    load_u(0, ur, ui);  // in flight with the tile's loads
 
     // Per-tile phase angles of the blocks carrying phase terms, in an LDS
     // table: row pslot holds the 16 column angles (front terms) and the 16
@@ -231,6 +238,8 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
         }
     };
 
+    // the first block's operands follow the tile's loads
+    auto first = [&]() { load_u(0, ur, ui); };
     tile_sweep<R, TA_LOG, PAIR, NTH, true>(st, a, tile, [&](C *t) {
         if (PHASES) {
             fill_angles();
@@ -303,7 +312,7 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
                 apply_phases(subs[sb + 1]);
             }
         }
-    });
+    }, SameSlot(), first);
 }
 
 // ---------------------------------------------------------------------------
@@ -417,18 +426,12 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
     const int lane = tid & 63;
     const int q = lane / 16, j16 = lane % 16;
 
-    const uint64_t tbase = insert_zeros(uint64_t(blockIdx.y) * gridDim.x + blockIdx.x, a.outer);
-    auto variant = [&](const PassSub &d) {
-        uint32_t var = 0;
-        for (uint32_t v = 0; v < d.nvar; ++v)
-            var |= uint32_t((tbase >> d.vpos[v]) & 1) << v;
-        return var;
-    };
+    const uint64_t tbase = insert_zeros_n<TA_LOG>(uint64_t(blockIdx.y) * gridDim.x + blockIdx.x, a.outer);
     // PHASES: this lane's FP32 fragment of block sb, U[j16][4 q + r], r < 4
     auto load_u = [&](int sb, float *ur, float *ui) {
         const PassSub &d = subs[sb];
         const float4 *U = reinterpret_cast<const float4 *>(reinterpret_cast<const C *>(mats + d.u_off) +
-                                                           size_t(variant(d)) * (D * D) + j16 * D + 4 * q);
+                                                           size_t(variant_of(tbase, d)) * (D * D) + j16 * D + 4 * q);
         const float4 u0 = U[0], u1 = U[1];
         ur[0] = u0.x;
         ui[0] = u0.y;
@@ -444,7 +447,7 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
     // each
     auto load_a = [&](int sb, uint32_t *A) {
         const PassSub &d = subs[sb];
-        const uint4 *P = reinterpret_cast<const uint4 *>(mats + d.u_off + size_t(variant(d)) * kPresplitBytes) + lane;
+        const uint4 *P = reinterpret_cast<const uint4 *>(mats + d.u_off + size_t(variant_of(tbase, d)) * kPresplitBytes) + lane;
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
             const uint4 v = P[i * 64];
@@ -456,10 +459,6 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
     };
     float ur[4], ui[4];
     uint32_t a0[24], a1[24];  // this block's and the next one's
-    if constexpr (PHASES)
-        load_u(0, ur, ui);  // in flight with the tile's loads
-    else
-        load_a(0, a0);
 
     // per-tile phase angles, as in k_pass (fixed-point turns, 32 bits)
     __shared__ uint32_t angles[PHASES ? kMaxTermBlocks * 32 : 1];
@@ -489,6 +488,13 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
         }
     };
 
+    // the first block's operands follow the tile's loads
+    auto first = [&]() {
+        if constexpr (PHASES)
+            load_u(0, ur, ui);
+        else
+            load_a(0, a0);
+    };
     tile_sweep<float, TA_LOG, true, NTH, true>(st, a, tile, [&](C *t) {
         if (PHASES) {
             fill_angles();
@@ -585,7 +591,7 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
                 }
             }
         }
-    });
+    }, SameSlot(), first);
 }
 
 template <typename R, int TA_LOG, int NTH>

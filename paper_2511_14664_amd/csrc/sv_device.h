@@ -14,7 +14,8 @@ namespace sv {
 namespace dev {
 
 constexpr int kThreads = 256;
-constexpr int kMaxIns = SV_MAX_TARGETS + SV_MAX_CONTROLS;
+constexpr int kMaxTileBits = 13;
+constexpr int kMaxIns = kMaxTileBits + SV_MAX_CONTROLS;  // a tile's bits and the controls outside it
 
 template <typename R>
 struct CT;
@@ -27,7 +28,8 @@ struct CT<double> {
     using C = double2;
 };
 
-// Insert a 0 bit at each of up to kMaxIns sorted positions: m[j] = 2^p_j - 1.
+// Insert a 0 bit at each of up to kMaxIns sorted positions: m[j] = 2^p_j - 1
+// (all ones, inserting nothing, from n on).
 struct InsertMasks {
     uint64_t m[kMaxIns];
     int n;
@@ -38,8 +40,8 @@ inline InsertMasks make_insert_masks(std::vector<int> pos)
     std::sort(pos.begin(), pos.end());
     InsertMasks im{};
     im.n = static_cast<int>(pos.size());
-    for (int j = 0; j < im.n; ++j)
-        im.m[j] = (uint64_t(1) << pos[j]) - 1;
+    for (int j = 0; j < kMaxIns; ++j)
+        im.m[j] = j < im.n ? (uint64_t(1) << pos[j]) - 1 : ~uint64_t(0);
     return im;
 }
 
@@ -52,14 +54,26 @@ __host__ __device__ __forceinline__ uint64_t insert_zeros(uint64_t g, const Inse
     return g;
 }
 
-// The same with im.n = N known: the masks come in a few wide scalar loads
-// instead of one load and wait each.
+// The same for im.n <= N: the masks come in a few wide scalar loads instead of
+// one load and wait each.
 template <int N>
 __device__ __forceinline__ uint64_t insert_zeros_n(uint64_t g, const InsertMasks &im)
 {
     static_assert(N <= kMaxIns, "masks");
 #pragma unroll
     for (int j = 0; j < N; ++j) {
+        const uint64_t lo = im.m[j];
+        g = (g & lo) | ((g & ~lo) << 1);
+    }
+    return g;
+}
+
+// Any im.n, fastest up to a 2^12 tile with two controls.
+__device__ __forceinline__ uint64_t insert_zeros_wide(uint64_t g, const InsertMasks &im)
+{
+    constexpr int N = 14;
+    g = insert_zeros_n<N>(g, im);
+    for (int j = N; j < im.n; ++j) {
         const uint64_t lo = im.m[j];
         g = (g & lo) | ((g & ~lo) << 1);
     }
@@ -121,9 +135,8 @@ struct TileArgs {
     uint64_t ntiles;
     uint64_t cmask;
     InsertMasks outer;                 // zeros at tile bits and control bits
-    uint64_t dep[13];                  // dep[b] = 2^(physical position of tile bit b)
+    uint64_t dep[kMaxTileBits];        // dep[b] = 2^(physical position of tile bit b)
     uint32_t tslot_m[SV_MAX_TARGETS];  // insert masks of the target slots in x
-    int ntslot;
     uint16_t xc[64];                   // x bits of target-row index r
     const void *U;
 };
@@ -155,7 +168,6 @@ inline TileArgs make_tile_args(int n, int k, const int *tgt, const int *ctl, int
         slot[b] = int(std::find(tilebits.begin(), tilebits.end(), tgt[b]) - tilebits.begin());
     std::vector<int> sorted_slots(slot, slot + k);
     std::sort(sorted_slots.begin(), sorted_slots.end());
-    a.ntslot = k;
     for (int b = 0; b < k; ++b)
         a.tslot_m[b] = (1u << sorted_slots[b]) - 1u;
     for (int r = 0; r < (1 << k); ++r) {
@@ -175,10 +187,12 @@ inline TileArgs make_tile_args(int n, int k, const int *tgt, const int *ctl, int
     return a;
 }
 
-// x-slot of group g: insert zeros at the target slots.
+// x-slot of group g: insert zeros at the K target slots.
+template <int K>
 __device__ __forceinline__ uint32_t group_slot(uint32_t g, const TileArgs &a)
 {
-    for (int s = 0; s < a.ntslot; ++s) {
+#pragma unroll
+    for (int s = 0; s < K; ++s) {
         const uint32_t lo = a.tslot_m[s];
         g = (g & lo) | ((g & ~lo) << 1);
     }
@@ -283,7 +297,7 @@ __device__ __forceinline__ void tile_sweep(R *__restrict__ st, const TileArgs &a
         return;
     const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(tid >> 6));
     // a pass tile (PSWZ) has no controls: its outer mask is the tile's bits
-    uint64_t base = PSWZ ? insert_zeros_n<TA_LOG>(o, a.outer) : insert_zeros(o, a.outer) | a.cmask;
+    uint64_t base = PSWZ ? insert_zeros_n<TA_LOG>(o, a.outer) : insert_zeros_wide(o, a.outer) | a.cmask;
 #pragma unroll
     for (int b = 6; b < TB; ++b)
         base |= a.dep[b + LO] & (0 - uint64_t((wave >> (b - 6)) & 1));

@@ -107,15 +107,18 @@ __global__ __launch_bounds__(kThreads) void k_dense_mfma(R *__restrict__ st, con
     const int bj = lane % NT, bkk = lane / NT;   // B operand coordinates
 
     // Each wave keeps one row block and takes every (4 / NMT)-th group set.
-    // Everything the products need besides the tile is fetched here, before
-    // the tile's loads, so that its latency hides under theirs: the U
-    // fragment of this lane, and the per-lane halves of the slot table.  Slot
+    // Everything the products need besides the tile is fetched behind the
+    // tile's loads, so that its latency hides under theirs: the U fragment of
+    // this lane, and the per-lane halves of the slot table.  Slot
     // lookups split as xc[r] = xc[r_lo] | xc[r_hi] (the deposit of disjoint
     // bits of r); the halves indexed by a compile-time or wave-uniform value
     // are scalar loads.
     const int mt = __builtin_amdgcn_readfirstlane(wave % NMT);
+    constexpr bool F64 = std::is_same<R, double>::value;
     R ur[NS], ui[NS];
-    {
+    uint32_t xb_lane = 0, xo_lane = 0, xo_mt = 0;
+    uint32_t xg[PER_WAVE];
+    auto first = [&]() {
         const C *Urow = U + size_t(mt * MT + ai) * D + akk;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
@@ -123,15 +126,13 @@ __global__ __launch_bounds__(kThreads) void k_dense_mfma(R *__restrict__ st, con
             ur[s] = u.x;
             ui[s] = u.y;
         }
-    }
-    constexpr bool F64 = std::is_same<R, double>::value;
-    const uint32_t xb_lane = a.xc[bkk];                            // k-step bits 0..1
-    const uint32_t xo_lane = a.xc[F64 ? (lane / 16) : 4 * (lane / 16)];  // output row, lane part
-    const uint32_t xo_mt = a.xc[mt * MT];                          // output row, row-block part
-    uint32_t xg[PER_WAVE];
+        xb_lane = a.xc[bkk];                                // k-step bits 0..1
+        xo_lane = a.xc[F64 ? (lane / 16) : 4 * (lane / 16)];  // output row, lane part
+        xo_mt = a.xc[mt * MT];                              // output row, row-block part
 #pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j)
-        xg[j] = group_slot(uint32_t((wave / NMT + (4 / NMT) * j) * NT + bj), a);
+        for (int j = 0; j < PER_WAVE; ++j)
+            xg[j] = group_slot<K>(uint32_t((wave / NMT + (4 / NMT) * j) * NT + bj), a);
+    };
 
     tile_sweep<R, TA_LOG, PAIR>(st, a, tile, [&](C *t) {
         AccT p1[PER_WAVE], p2[PER_WAVE], p3[PER_WAVE];
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void k_dense_mfma(R *__restrict__ st, con
             }
         }
         __syncthreads();
-    });
+    }, SameSlot(), first);
 }
 
 template <typename R, int K, int TA_LOG = MfmaTile<R, K>::TA_LOG>
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void k_dense_bf16x3(float *__restrict__ s
     const int mt = wave % NMT;
     const int gs = wave / NMT;
     const int i = lane % 32, kb = 8 * (lane / 32);
-    const uint32_t xg = group_slot(uint32_t(gs * 32 + i), a);
+    const uint32_t xg = group_slot<K>(uint32_t(gs * 32 + i), a);
 
     bf16x8 urh[NKC], url[NKC], uih[NKC], uil[NKC];
 #pragma unroll

@@ -448,7 +448,7 @@ __global__ __launch_bounds__(kThreads) void k_tile(R *__restrict__ st, const Til
     for (int j = 0; j < S::PAIRS; ++j) {
         const int p = wave + 4 * j;
         rb[j] = p / S::GCH;
-        xg[j] = group_slot(uint32_t((p % S::GCH) * 64 + lane), a);
+        xg[j] = group_slot<K>(uint32_t((p % S::GCH) * 64 + lane), a);
     }
 
     tile_sweep<R, S::TA_LOG, PAIR>(st, a, tile, [&](C *t) {

@@ -384,6 +384,11 @@ Block fuse(const std::vector<const Block *> &members, uint64_t qmask, bool dense
         }
     out.k = kb;
     out.c = 0;
+    if (kb == 0) {  // every gate of the block acts outside the tile: no members, the scalar 1
+        out.U.assign(1, cd(1.0, 0.0));
+        out.diag = true;
+        return out;
+    }
     const int d = 1 << kb;
     // Every position starts as a factor of its own; a gate joins the factors
     // of its qubits and multiplies into the joint one, so a gate's cost is that

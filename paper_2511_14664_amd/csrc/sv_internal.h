@@ -224,8 +224,20 @@ struct PassSub {
     uint32_t nvar;        // matrix variants 2^nvar, selected by the tile's index bits vpos
     uint64_t vpos;        // byte j: position of bit j of the variant number
     uint32_t pslot;       // with nterm > 0: this block's row of the per-tile angle table (< kMaxTermBlocks)
-    uint32_t pad;
+    uint32_t diag;        // no matrix: a diagonal step, its terms coefficients at diag_entry()
 };
+// Coefficient table of a diagonal step on a tile (kDiagRows rows of the angle
+// table): entry 0 the constant, then one per tile bit and one per pair i < j.
+constexpr int kDiagRows = 3;
+constexpr int diag_entry(int bit)
+{
+    return 1 + bit;
+}
+constexpr int diag_entry(int i, int j)
+{
+    return 14 + j * (j - 1) / 2 + i;
+}
+static_assert(diag_entry(11, 12) < kDiagRows * 32, "pairs of 13 tile bits fit");
 // Lay out a block on the tile slots slots[0..4): order[b] is the index into
 // slots of row bit b, chosen with the lanes' group bits so that the kernel's
 // LDS accesses spread over all banks where the slots allow it; fills d.rx, d.gx.

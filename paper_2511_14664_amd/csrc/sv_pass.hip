@@ -137,6 +137,67 @@ __device__ __forceinline__ void lds_add(uint64_t *p, uint64_t v)
     atomicAdd(reinterpret_cast<unsigned long long *>(p), static_cast<unsigned long long>(v));
 }
 
+// Diagonal step of a complex64 tile: amplitude x times exp(2 pi i f(x)), f a
+// constant, one coefficient per tile bit and one per pair of bits (row: fixed
+// point turns at diag_entry()), summed exactly.  The angles of a thread's
+// amplitudes start from the sum over its thread bits and grow by one addition
+// each over the bits its accesses differ in; then a sine and a cosine and one
+// complex product per amplitude, on the vector unit.  About 1.4 split blocks or
+// one FP32 block, whatever the number of gates (a QFT pass held up to ten
+// blocks of nothing else).
+template <int TA_LOG, int NTH>
+__device__ __forceinline__ void diag_step(float2 *tile, const uint32_t *row, int tid)
+{
+    constexpr int TB = NTH == 512 ? 9 : 8;
+    constexpr int NB = TA_LOG - TB;  // bits of a thread's amplitudes: 0 and the highest
+    auto reg = [](int b) { return b == 0 ? 0 : TB + b; };
+    uint32_t m[TB];  // thread bit k is tile bit k + 1
+#pragma unroll
+    for (int k = 0; k < TB; ++k)
+        m[k] = uint32_t(-((tid >> k) & 1));
+    uint32_t f[1 << NB];
+    f[0] = row[0];
+#pragma unroll
+    for (int l = 0; l < TB; ++l) {
+        uint32_t s = row[diag_entry(l + 1)];
+#pragma unroll
+        for (int k = 0; k < l; ++k)
+            s += row[diag_entry(k + 1, l + 1)] & m[k];
+        f[0] += s & m[l];
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        __builtin_amdgcn_sched_barrier(0);  // not every coefficient in registers at once
+        uint32_t s = row[diag_entry(reg(b))];
+#pragma unroll
+        for (int k = 0; k < TB; ++k)
+            s += row[k + 1 < reg(b) ? diag_entry(k + 1, reg(b)) : diag_entry(reg(b), k + 1)] & m[k];
+        // over the amplitudes with lower register bits e
+        uint32_t c[1 << NB];
+        c[0] = s;
+#pragma unroll
+        for (int a = 0; a < b; ++a)
+#pragma unroll
+            for (int e = 0; e < (1 << a); ++e)
+                c[e | 1 << a] = c[e] + row[diag_entry(reg(a), reg(b))];
+#pragma unroll
+        for (int e = 0; e < (1 << b); ++e)
+            f[e | 1 << b] = f[e] + c[e];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t slot = swz_p<float>(uint32_t(tid) << 1) << 3;
+#pragma unroll
+    for (int s = 0; s < (1 << NB) / 2; ++s) {
+        float4 *p = reinterpret_cast<float4 *>(reinterpret_cast<char *>(tile) +
+                                               (slot ^ (swz_p<float>(uint32_t(s * NTH) << 1) << 3)));
+        const float4 v = *p;
+        float s0, c0, s1, c1;
+        turn_sincos(f[2 * s], s0, c0);
+        turn_sincos(f[2 * s + 1], s1, c1);
+        *p = make_float4(v.x * c0 - v.y * s0, v.x * s0 + v.y * c0, v.z * c1 - v.w * s1, v.z * s1 + v.w * c1);
+    }
+}
+
 // Residency target: five workgroups per CU fill the LDS with 32 KiB tiles,
 // so the complex64 256-thread kernel without phase terms is held to 96
 // registers (which also keeps the matrix products in VGPR form, without
@@ -181,6 +242,8 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
             xi[s] = u.y;
         }
     };
+    // a diagonal step (complex64 passes with phases) has no matrix
+    auto has_matrix = [&](int sb) { return !(PHASES && !F64 && subs[sb].diag); };
     R ur[NS], ui[NS];
 
     // Per-tile phase angles of the blocks carrying phase terms, in an LDS
@@ -202,13 +265,15 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
                 continue;
             const PassTerm *tm = reinterpret_cast<const PassTerm *>(mats + d.t_off);
             TurnT *row = angles + d.pslot * 32;
-            if (lane < 32)
-                row[lane] = 0;
+            for (int k = lane; k < (d.diag ? kDiagRows * 32 : 32); k += 64)
+                row[k] = 0;
             for (uint32_t e = uint32_t(lane); e < d.nterm; e += 64) {
                 const PassTerm t = tm[e];
                 if ((tbase & t.omask) == t.omask)
                     lds_add(&row[t.back * 16 + t.smask], TurnT(F64 ? t.turn : (t.turn >> 32)));
             }
+            if (d.diag)
+                continue;  // coefficients, not sums
             // this wave's LDS operations complete in order: the entries are final
             TurnT acc = lane < 32 ? row[lane] : TurnT(0);
 #pragma unroll
@@ -224,7 +289,7 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
     // U[r][c] * exp(i (front(c) + back(r))) for this lane's fragment of a
     // block carrying phase terms (table filled for this tile)
     auto apply_phases = [&](const PassSub &d) {
-        if (PHASES && d.nterm > 0) {
+        if (PHASES && d.nterm > 0 && !d.diag) {
             const TurnT *row = angles + d.pslot * 32;
             const TurnT tb = row[16 + ai];
 #pragma unroll
@@ -239,7 +304,10 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
     };
 
     // the first block's operands follow the tile's loads
-    auto first = [&]() { load_u(0, ur, ui); };
+    auto first = [&]() {
+        if (has_matrix(0))
+            load_u(0, ur, ui);
+    };
     tile_sweep<R, TA_LOG, PAIR, NTH, true>(st, a, tile, [&](C *t) {
         if (PHASES) {
             fill_angles();
@@ -250,9 +318,23 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
         apply_phases(subs[0]);
         for (int sb = 0; sb < nsub; ++sb) {
             R nr[NS], ni[NS];
-            if (sb + 1 < nsub)
+            if (sb + 1 < nsub && has_matrix(sb + 1))
                 load_u(sb + 1, nr, ni);
             const PassSub &d = subs[sb];
+            if constexpr (PHASES && !F64)
+                if (d.diag) {
+                    diag_step<TA_LOG, NTH>(t, angles + d.pslot * 32, tid);
+                    __syncthreads();
+                    if (sb + 1 < nsub && has_matrix(sb + 1)) {
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) {
+                            ur[s] = nr[s];
+                            ui[s] = ni[s];
+                        }
+                        apply_phases(subs[sb + 1]);
+                    }
+                    continue;
+                }
             // LDS addresses.  The byte offset of a (row, group) is linear over
             // XOR in its bits (d.rx, d.gx: swizzled), and the bits are the
             // lane's (row bits from bkk or the accumulator row, group bits
@@ -303,7 +385,7 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
                 }
             }
             __syncthreads();
-            if (sb + 1 < nsub) {
+            if (sb + 1 < nsub && has_matrix(sb + 1)) {
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     ur[s] = nr[s];
@@ -408,7 +490,7 @@ __device__ __forceinline__ floatx4 mma_split6(const uint32_t *ah, const uint32_t
 // CU, for passes of several blocks) or 512 (three, for one-block passes only,
 // which are bound by HBM: 8 waves share a tile's loads and its one block).
 template <bool PHASES, int NTH>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NTH == 256 ? (PHASES ? 4 : 5) : 1)))
+__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(PHASES ? 4 : (NTH == 256 ? 5 : 1))))
 void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__restrict__ subs, int nsub,
                   const char *__restrict__ mats)
 {
@@ -469,13 +551,15 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
                 continue;
             const PassTerm *tm = reinterpret_cast<const PassTerm *>(mats + d.t_off);
             uint32_t *row = angles + d.pslot * 32;
-            if (lane < 32)
-                row[lane] = 0;
+            for (int k = lane; k < (d.diag ? kDiagRows * 32 : 32); k += 64)
+                row[k] = 0;
             for (uint32_t e = uint32_t(lane); e < d.nterm; e += 64) {
                 const PassTerm t = tm[e];
                 if ((tbase & t.omask) == t.omask)
                     lds_add(&row[t.back * 16 + t.smask], uint32_t(t.turn >> 32));
             }
+            if (d.diag)
+                continue;  // coefficients, not sums
             uint32_t acc = lane < 32 ? row[lane] : 0u;
 #pragma unroll
             for (int bit = 1; bit < 16; bit <<= 1) {
@@ -490,10 +574,12 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
 
     // the first block's operands follow the tile's loads
     auto first = [&]() {
-        if constexpr (PHASES)
-            load_u(0, ur, ui);
-        else
+        if constexpr (PHASES) {
+            if (!subs[0].diag)
+                load_u(0, ur, ui);
+        } else {
             load_a(0, a0);
+        }
     };
     tile_sweep<float, TA_LOG, true, NTH, true>(st, a, tile, [&](C *t) {
         if (PHASES) {
@@ -571,10 +657,17 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
         };
         if constexpr (PHASES) {
             for (int sb = 0; sb < nsub; ++sb) {
-                split_u(sb, a0);
-                if (sb + 1 < nsub)
+                const bool diag = subs[sb].diag != 0;
+                if (!diag)
+                    split_u(sb, a0);
+                if (sb + 1 < nsub && !subs[sb + 1].diag)
                     load_u(sb + 1, ur, ui);
-                block(sb, a0);
+                if (diag) {
+                    diag_step<TA_LOG, NTH>(t, angles + subs[sb].pslot * 32, tid);
+                    __syncthreads();
+                } else {
+                    block(sb, a0);
+                }
             }
         } else if constexpr (NTH == 512) {
             block(0, a0);  // one-block passes only: no second operand set

@@ -86,19 +86,32 @@ __device__ __forceinline__ void turn_sincos(uint32_t u, float &sn, float &cs)
 }
 
 // The same for 2 pi u / 2^64 in FP64: Taylor terms through x^17 (sin) and
-// x^18 (cos), truncation error below (pi/4)^19 / 19! = 2e-19.
+// x^18 (cos), truncation error below (pi/4)^19 / 19! = 2e-19.  (Horner with
+// rounded coefficients; a quotient per term took five times the instructions.)
 __device__ __forceinline__ void turn_sincos(uint64_t u, double &sn, double &cs)
 {
     const uint64_t k = (u + (uint64_t(1) << 61)) >> 62;
     const double x = double(int64_t(u - (k << 62))) * (2.0 * M_PI / 18446744073709551616.0);
     const double x2 = x * x;
-    double s = 1.0, c = 1.0;
-    // Horner from the highest term: sin = x sum (-x2)^j / (2j+1)!, cos = sum (-x2)^j / (2j)!
-    for (int j = 8; j >= 1; --j)
-        s = 1.0 - x2 / double((2 * j) * (2 * j + 1)) * s;
-    for (int j = 9; j >= 1; --j)
-        c = 1.0 - x2 / double((2 * j - 1) * (2 * j)) * c;
-    s *= x;
+    // signed reciprocal factorials
+    double s = 1.0 / 355687428096000.0, c = -1.0 / 6402373705728000.0;
+    s = fma(s, x2, -1.0 / 1307674368000.0);
+    s = fma(s, x2, 1.0 / 6227020800.0);
+    s = fma(s, x2, -1.0 / 39916800.0);
+    s = fma(s, x2, 1.0 / 362880.0);
+    s = fma(s, x2, -1.0 / 5040.0);
+    s = fma(s, x2, 1.0 / 120.0);
+    s = fma(s, x2, -1.0 / 6.0);
+    s = fma(s * x2, x, x);
+    c = fma(c, x2, 1.0 / 20922789888000.0);
+    c = fma(c, x2, -1.0 / 87178291200.0);
+    c = fma(c, x2, 1.0 / 479001600.0);
+    c = fma(c, x2, -1.0 / 3628800.0);
+    c = fma(c, x2, 1.0 / 40320.0);
+    c = fma(c, x2, -1.0 / 720.0);
+    c = fma(c, x2, 1.0 / 24.0);
+    c = fma(c, x2, -0.5);
+    c = fma(c, x2, 1.0);
     sn = (k & 1) ? c : s;
     cs = (k & 1) ? s : c;
     if (k & 2)
@@ -144,17 +157,16 @@ __device__ __forceinline__ void lds_add(uint64_t *p, uint64_t v)
 // each over the bits its accesses differ in; then a sine and a cosine and one
 // complex product per amplitude, on the vector unit.  About 1.4 split blocks or
 // one FP32 block, whatever the number of gates (a QFT pass held up to ten
-// blocks of nothing else).
+// blocks of nothing else).  In FP64 the kernel would spill (130 registers at
+// the four workgroups per CU it needs) and whole QFTs ran 0.88 times as fast.
 template <int TA_LOG, int NTH>
 __device__ __forceinline__ void diag_step(float2 *tile, const uint32_t *row, int tid)
 {
     constexpr int TB = NTH == 512 ? 9 : 8;
     constexpr int NB = TA_LOG - TB;  // bits of a thread's amplitudes: 0 and the highest
     auto reg = [](int b) { return b == 0 ? 0 : TB + b; };
-    uint32_t m[TB];  // thread bit k is tile bit k + 1
-#pragma unroll
-    for (int k = 0; k < TB; ++k)
-        m[k] = uint32_t(-((tid >> k) & 1));
+    // x where thread bit k (tile bit k + 1) is set
+    auto where = [&](uint32_t x, int k) { return x & uint32_t(-((tid >> k) & 1)); };
     uint32_t f[1 << NB];
     f[0] = row[0];
 #pragma unroll
@@ -162,16 +174,17 @@ __device__ __forceinline__ void diag_step(float2 *tile, const uint32_t *row, int
         uint32_t s = row[diag_entry(l + 1)];
 #pragma unroll
         for (int k = 0; k < l; ++k)
-            s += row[diag_entry(k + 1, l + 1)] & m[k];
-        f[0] += s & m[l];
+            s += where(row[diag_entry(k + 1, l + 1)], k);
+        f[0] += where(s, l);
+        __builtin_amdgcn_sched_barrier(0);  // not every coefficient in registers at once
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        __builtin_amdgcn_sched_barrier(0);  // not every coefficient in registers at once
+        __builtin_amdgcn_sched_barrier(0);
         uint32_t s = row[diag_entry(reg(b))];
 #pragma unroll
         for (int k = 0; k < TB; ++k)
-            s += row[k + 1 < reg(b) ? diag_entry(k + 1, reg(b)) : diag_entry(reg(b), k + 1)] & m[k];
+            s += where(row[k + 1 < reg(b) ? diag_entry(k + 1, reg(b)) : diag_entry(reg(b), k + 1)], k);
         // over the amplitudes with lower register bits e
         uint32_t c[1 << NB];
         c[0] = s;

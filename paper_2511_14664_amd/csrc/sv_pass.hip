@@ -434,8 +434,15 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
 // A[j][8 q + 2 r + c] of tile t holds U entries of row 4 (j / 4) + 2 t +
 // j % 4 / 2, column 4 q + r.  Products are accumulated smallest first.
 //
-// Vector instructions bound the kernel (a wave's 12 matrix products of a
-// group set take 192 cycles, 69 vector instructions 276): XXX
+// What bounds it: the matrix products of a group set take 192 cycles of a SIMD,
+// and each also takes issue slots from the 52 other vector instructions (44 of
+// them the splits); both together run in 338 cycles with five waves per SIMD and
+// nothing else in the loop.  On 28 qubits a pass of one block takes 0.69 ms (the
+// copy rate), of two to five 0.80, 0.90, 1.02 and 1.17; with outputs moved into
+// adjacent registers, operands copied between blocks, group bits in ascending
+// order on the lanes and masks read one by one (69 instructions per group set,
+// 268 instead of 105 for a wave's share of a tile's loads and stores, half the
+// LDS cycles bank conflicts) 0.69, 0.81, 0.93, 1.17 and 1.41.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));

@@ -756,7 +756,8 @@ __global__ __launch_bounds__(kThreads) void k_block_sums(const R *__restrict__ s
 // chunk's start, the shot takes the chunk's last block of nonzero total, and a
 // target at or past the total the last such block of all, each with that total
 // as residual.
-// (One thread adding up all 1024 chunks took most of 47 us at 2^14 blocks.)
+// (One thread adding up all 1024 chunks took most of 47 us at 2^14 blocks; now
+// 16.)
 constexpr int kPrepThreads = 1024;
 constexpr int kPrepGroup = 32;
 
@@ -882,8 +883,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_sample_prep(const double *__re
 // amplitude of nonzero probability whose in-block running sum exceeds the
 // residual target.  If rounding leaves none, the last index of nonzero
 // probability seen is returned.  (Walking from the block's start, each segment
-// waits for memory: 73 us for 1024 shots in 2^14-amplitude blocks at 28
-// qubits.)
+// waits for memory: 73 us for 1000 shots in 2^14-amplitude blocks at 28 qubits,
+// against 31.)
 constexpr int kSearchSegLog = 10;
 constexpr int kSearchMaxLog = 16;
 

@@ -274,7 +274,8 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
     auto fill_angles = [&]() {
         for (int sb = 0; sb < nsub; ++sb) {
             const PassSub &d = subs[sb];
-            if (d.nterm == 0 || int(d.pslot % NW) != wave)
+            // a diagonal step reads its rows also where no term is left
+            if ((d.nterm == 0 && !d.diag) || int(d.pslot % NW) != wave)
                 continue;
             const PassTerm *tm = reinterpret_cast<const PassTerm *>(mats + d.t_off);
             TurnT *row = angles + d.pslot * 32;
@@ -567,7 +568,8 @@ void k_pass_split(float *__restrict__ st, const TileArgs a, const PassSub *__res
     auto fill_angles = [&]() {
         for (int sb = 0; sb < nsub; ++sb) {
             const PassSub &d = subs[sb];
-            if (d.nterm == 0 || int(d.pslot % NW) != wave)
+            // a diagonal step reads its rows also where no term is left
+            if ((d.nterm == 0 && !d.diag) || int(d.pslot % NW) != wave)
                 continue;
             const PassTerm *tm = reinterpret_cast<const PassTerm *>(mats + d.t_off);
             uint32_t *row = angles + d.pslot * 32;

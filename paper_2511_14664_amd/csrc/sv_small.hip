@@ -22,9 +22,14 @@
 // uniform dispatch on each gate's target and controls took 0.75 us a gate.
 //
 // Steps use the arithmetic of the per-launch kernels: one-target gates as
-// complex 2 x 2 products, blocks of four to six targets as three real products
-// on the FP32 / FP64 matrix cores, blocks of two and three targets on the
-// vector unit.
+// complex 2 x 2 products, blocks of two targets (three below 8 qubits) on the
+// vector unit, wider ones on the FP32 / FP64 matrix cores.  A complex product
+// is three real ones where the launch of that size takes three (complex64 from
+// 12 qubits on, complex128 from 10, for five and six targets from 11); below,
+// the launches multiply on the vector unit with four, and the steps take four
+// sums, one per product (three products, or the four in two sums, would raise
+// the error of a block by a factor of up to 1.4: the vector unit adds the two
+// products of a term before it adds them to the sum).
 #include <cstring>
 
 #include "sv_device.h"
@@ -43,9 +48,12 @@ enum : uint32_t {
     kStepDense2 = 1,  // two targets, one group per thread
     kStepDense3 = 2,
     kStepDense = 3,   // any width, one output per thread: few groups, or controls
-    kStepMfma4 = 4,   // four, five, six targets on the matrix cores
+    kStepMfma4 = 4,   // four, five, six targets on the matrix cores, four real products
     kStepMfma5 = 5,
     kStepMfma6 = 6,
+    kStepMfma4t = 7,  // the same in three real products
+    kStepMfma5t = 8,
+    kStepMfma6t = 9,
 };
 
 // One step of two or more targets.
@@ -309,8 +317,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
         // Matrix cores: item (group set of 16 groups, row block of 16 rows);
         // every wave keeps one row block.  mbuf holds the A operands in the
         // order (row block, k-step, lane): U[16 mt + lane % 16][4 s + lane / 16].
-        auto mfma_items = [&](auto k_tag, auto p_tag) __attribute__((always_inline)) {
+        auto mfma_items = [&](auto k_tag, auto p_tag, auto three_tag) __attribute__((always_inline)) {
             constexpr int K = decltype(k_tag)::value, D = 1 << K, NS = D / 4, NMT = D / 16;
+            constexpr bool THREE = decltype(three_tag)::value;
             constexpr int PW = decltype(p_tag)::value;  // items per wave
             const bool active = wave < (cnt / 16) * NMT;  // (PW > 1: every wave)
             const uint32_t mt = wave % NMT;
@@ -327,7 +336,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
             const uint32_t out_lane = F64 ? in_lane : slot(((q & 1) ? target(2) : 0u) | ((q & 2) ? target(3) : 0u));
             const uint32_t own_j = slot(dep(lane % 16) | ones);
             uint32_t go[PW];
-            AccT p1[PW], p2[PW], p3[PW];
+            // THREE: sums of ur xr, ui xi, (ur + ui) (xr + xi); else of ur xr, ui xi, ur xi, ui xr
+            AccT p1[PW], p2[PW], p3[PW], p4[PW];
             if (active) {
 #pragma unroll
                 for (int j = 0; j < PW; ++j) {
@@ -335,6 +345,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
                     p1[j] = AccT{};
                     p2[j] = AccT{};
                     p3[j] = AccT{};
+                    p4[j] = AccT{};
                 }
 #pragma unroll 4
                 for (int t = 0; t < NS; ++t) {
@@ -346,7 +357,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
                         const C x = at(go[j] ^ in_lane ^ ss);
                         p1[j] = mma(u.x, x.x, p1[j]);
                         p2[j] = mma(u.y, x.y, p2[j]);
-                        p3[j] = mma(us, x.x + x.y, p3[j]);
+                        if constexpr (THREE) {
+                            p3[j] = mma(us, x.x + x.y, p3[j]);
+                        } else {
+                            p3[j] = mma(u.x, x.y, p3[j]);
+                            p4[j] = mma(u.y, x.x, p4[j]);
+                        }
                     }
                 }
             }
@@ -360,21 +376,26 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
                         const uint32_t rr = slot(row(16 * mt + uint32_t(F64 ? 4 * r : r)));
                         C y;
                         y.x = p1[j][r] - p2[j][r];
-                        y.y = p3[j][r] - p1[j][r] - p2[j][r];
+                        y.y = THREE ? p3[j][r] - p1[j][r] - p2[j][r] : p3[j][r] + p4[j][r];
                         at(go[j] ^ out_lane ^ rr) = y;
                     }
             }
         };
         // 2^(n - 8) items: two per wave at 13 qubits, else at most one
-        auto mfma_dense = [&](auto k_tag) __attribute__((always_inline)) {
-            mfma_items(k_tag, std::integral_constant<int, U == 4 ? 2 : 1>{});
+        auto mfma_dense = [&](auto k_tag, auto three_tag) __attribute__((always_inline)) {
+            // (12 qubits and more: three products always; below, complex64: never)
+            if constexpr (decltype(three_tag)::value ? F64 || U > 1 : U == 1)
+                mfma_items(k_tag, std::integral_constant<int, U == 4 ? 2 : 1>{}, three_tag);
         };
         switch (kind) {
         case kStepDense2: small_dense(std::integral_constant<int, 2>{}); break;
         case kStepDense3: small_dense(std::integral_constant<int, 3>{}); break;
-        case kStepMfma4: mfma_dense(std::integral_constant<int, 4>{}); break;
-        case kStepMfma5: mfma_dense(std::integral_constant<int, 5>{}); break;
-        case kStepMfma6: mfma_dense(std::integral_constant<int, 6>{}); break;
+        case kStepMfma4: mfma_dense(std::integral_constant<int, 4>{}, std::false_type{}); break;
+        case kStepMfma5: mfma_dense(std::integral_constant<int, 5>{}, std::false_type{}); break;
+        case kStepMfma6: mfma_dense(std::integral_constant<int, 6>{}, std::false_type{}); break;
+        case kStepMfma4t: mfma_dense(std::integral_constant<int, 4>{}, std::true_type{}); break;
+        case kStepMfma5t: mfma_dense(std::integral_constant<int, 5>{}, std::true_type{}); break;
+        case kStepMfma6t: mfma_dense(std::integral_constant<int, 6>{}, std::true_type{}); break;
         default: {
             // output (group, row) per thread, at most 2^12 / 1024 = 4 of them
             const uint32_t k = (kw >> 8) & 255u, D = 1u << k, outs = cnt << k;
@@ -423,13 +444,16 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
         go[i] = *reinterpret_cast<const uint4 *>(tile + slot(i * PERV));
 }
 
-uint32_t step_kind(int n, const Block &b)
+uint32_t step_kind(int n, int dtype, const Block &b)
 {
     if (b.k == 1)
         return kStepGate;
     if (b.k <= 3 && b.k + b.c <= 6)
         return b.k == 2 ? kStepDense2 : kStepDense3;
-    return b.c == 0 && b.k >= 4 && n - b.k >= 4 ? kStepMfma4 + uint32_t(b.k - 4) : kStepDense;
+    if (b.c != 0 || n - b.k < 4)
+        return kStepDense;
+    const bool three = dense_path(n, dtype, b.k, 0, SV_PREC_NATIVE) == SV_SWEEP_DENSE_MFMA;
+    return (three ? kStepMfma4t : kStepMfma4) + uint32_t(b.k - 4);
 }
 
 uint64_t large_bytes(int dtype, int k)
@@ -520,7 +544,7 @@ void small_add(SmallProgram &p, const Block &b, const int *pt, const int *pc)
         fixed |= 1u << pc[j];
     for (int j = 0; j < b.k; ++j)
         bits |= 1u << pt[j];
-    const uint32_t kind = step_kind(p.n, b);
+    const uint32_t kind = step_kind(p.n, p.dtype, b);
     char *rec = record(p, p.count);
     if (kind == kStepGate) {
         SmallGate g{};

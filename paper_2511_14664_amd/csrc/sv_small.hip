@@ -631,8 +631,11 @@ hipError_t launch_small(void *st, const SmallProgram &p, const void *blob, hipSt
         using R = decltype(r_tag);
         constexpr int U = decltype(u_tag)::value;
         if (lds > 65536) {
+            // always the most that a program takes: the attribute belongs to the
+            // process, and another thread's smaller program must not lower it
+            // between this and the launch
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_small<R, U>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsBytes));
             if (e != hipSuccess)
                 return e;
         }

@@ -47,7 +47,7 @@ enum : uint32_t {
     kStepGate = 0,    // one target, any controls
     kStepDense2 = 1,  // two targets, one group per thread
     kStepDense3 = 2,
-    kStepDense = 3,   // any width, one output per thread: few groups, or controls
+    kStepDense = 3,   // any width, one output per thread: fewer than 16 groups, or many controls
     kStepMfma4 = 4,   // four, five, six targets on the matrix cores, four real products
     kStepMfma5 = 5,
     kStepMfma6 = 6,
@@ -317,11 +317,18 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
         // Matrix cores: item (group set of 16 groups, row block of 16 rows);
         // every wave keeps one row block.  mbuf holds the A operands in the
         // order (row block, k-step, lane): U[16 mt + lane % 16][4 s + lane / 16].
+        // Controls are fixed bits of the group index, as in every step.  (One
+        // output per thread on the vector unit took 8 us for four targets and
+        // one control at 11 qubits, 32 at 13 and 120 for six targets, where a
+        // launch takes 6 to 15.)
         auto mfma_items = [&](auto k_tag, auto p_tag, auto three_tag) __attribute__((always_inline)) {
             constexpr int K = decltype(k_tag)::value, D = 1 << K, NS = D / 4, NMT = D / 16;
             constexpr bool THREE = decltype(three_tag)::value;
             constexpr int PW = decltype(p_tag)::value;  // items per wave
-            const bool active = wave < (cnt / 16) * NMT;  // (PW > 1: every wave)
+            const uint32_t items = (cnt / 16) * NMT;
+            const bool active = wave < items;
+            const bool all = PW == 1 || items > kSmallWaves;  // else only the first of a wave's items
+            auto dep_c = [&](uint32_t j) __attribute__((always_inline)) { return nins > 6 ? dep_any(j) : dep(j); };
             const uint32_t mt = wave % NMT;
             auto row = [&](uint32_t r) __attribute__((always_inline)) {
                 uint32_t x = 0;
@@ -334,14 +341,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
             const uint32_t q = lane / 16;
             const uint32_t in_lane = slot(((q & 1) ? target(0) : 0u) | ((q & 2) ? target(1) : 0u));
             const uint32_t out_lane = F64 ? in_lane : slot(((q & 1) ? target(2) : 0u) | ((q & 2) ? target(3) : 0u));
-            const uint32_t own_j = slot(dep(lane % 16) | ones);
+            const uint32_t own_j = slot(dep_c(lane % 16) | ones);
             uint32_t go[PW];
             // THREE: sums of ur xr, ui xi, (ur + ui) (xr + xi); else of ur xr, ui xi, ur xi, ui xr
             AccT p1[PW], p2[PW], p3[PW], p4[PW];
             if (active) {
 #pragma unroll
                 for (int j = 0; j < PW; ++j) {
-                    go[j] = own_j ^ slot(dep(((wave + uint32_t(kSmallWaves * j)) / NMT) * 16));
+                    go[j] = own_j ^ slot(dep_c(((wave + uint32_t(kSmallWaves * j)) / NMT) * 16));
                     p1[j] = AccT{};
                     p2[j] = AccT{};
                     p3[j] = AccT{};
@@ -354,6 +361,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
                     const uint32_t ss = slot(row(uint32_t(4 * t)));
 #pragma unroll
                     for (int j = 0; j < PW; ++j) {
+                        if (j > 0 && !all)
+                            break;
                         const C x = at(go[j] ^ in_lane ^ ss);
                         p1[j] = mma(u.x, x.x, p1[j]);
                         p2[j] = mma(u.y, x.y, p2[j]);
@@ -369,7 +378,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
             __syncthreads();  // every row block has read its groups
             if (active) {
 #pragma unroll
-                for (int j = 0; j < PW; ++j)
+                for (int j = 0; j < PW; ++j) {
+                    if (j > 0 && !all)
+                        break;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         // accumulator row: 4 (lane / 16) + r (FP32), 4 r + lane / 16 (FP64)
@@ -379,13 +390,15 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
                         y.y = THREE ? p3[j][r] - p1[j][r] - p2[j][r] : p3[j][r] + p4[j][r];
                         at(go[j] ^ out_lane ^ rr) = y;
                     }
+                }
             }
         };
-        // 2^(n - 8) items: two per wave at 13 qubits, else at most one
+        // 2^(n - 8 - controls) items: two per wave at 13 qubits without
+        // controls, where complex64 takes three products; else at most one
         auto mfma_dense = [&](auto k_tag, auto three_tag) __attribute__((always_inline)) {
-            // (12 qubits and more: three products always; below, complex64: never)
-            if constexpr (decltype(three_tag)::value ? F64 || U > 1 : U == 1)
-                mfma_items(k_tag, std::integral_constant<int, U == 4 ? 2 : 1>{}, three_tag);
+            constexpr bool THREE = decltype(three_tag)::value;
+            if constexpr (!THREE || F64 || U > 1)  // complex64 below 12 qubits: never three
+                mfma_items(k_tag, std::integral_constant<int, U == 4 && THREE ? 2 : 1>{}, three_tag);
         };
         switch (kind) {
         case kStepDense2: small_dense(std::integral_constant<int, 2>{}); break;
@@ -450,9 +463,9 @@ uint32_t step_kind(int n, int dtype, const Block &b)
         return kStepGate;
     if (b.k <= 3 && b.k + b.c <= 6)
         return b.k == 2 ? kStepDense2 : kStepDense3;
-    if (b.c != 0 || n - b.k < 4)
+    if (b.k < 4 || n - b.k - b.c < 4)
         return kStepDense;
-    const bool three = dense_path(n, dtype, b.k, 0, SV_PREC_NATIVE) == SV_SWEEP_DENSE_MFMA;
+    const bool three = dense_path(n, dtype, b.k, b.c, SV_PREC_NATIVE) == SV_SWEEP_DENSE_MFMA;
     return (three ? kStepMfma4t : kStepMfma4) + uint32_t(b.k - 4);
 }
 

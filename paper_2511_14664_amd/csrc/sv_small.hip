@@ -317,10 +317,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(R *__restrict__ st, con
         // Matrix cores: item (group set of 16 groups, row block of 16 rows);
         // every wave keeps one row block.  mbuf holds the A operands in the
         // order (row block, k-step, lane): U[16 mt + lane % 16][4 s + lane / 16].
-        // Controls are fixed bits of the group index, as in every step.  (One
-        // output per thread on the vector unit took 8 us for four targets and
-        // one control at 11 qubits, 32 at 13 and 120 for six targets, where a
-        // launch takes 6 to 15.)
+        // Controls are fixed bits of the group index, as in every step.  (With
+        // one control, four targets take 2.2 us at 11 qubits and 3.4 at 13, six
+        // targets 8.6 at 13; one output per thread on the vector unit took 9,
+        // 32 and 120, a launch each 9, 7 and 15.)
         auto mfma_items = [&](auto k_tag, auto p_tag, auto three_tag) __attribute__((always_inline)) {
             constexpr int K = decltype(k_tag)::value, D = 1 << K, NS = D / 4, NMT = D / 16;
             constexpr bool THREE = decltype(three_tag)::value;

@@ -657,102 +657,8 @@ struct PassWork : PassGroup {
     uint64_t nterm_max = 0;  // bound on the pass's phase terms
     bool split = false;      // complex64 blocks as split BF16 products (SV_PREC_BF16X6)
     bool presplit = false;   // split, no phase terms: matrices staged split (pass_presplit)
-    // the kernel's steps: one block each, or a diagonal step for all the phase
-    // gates of several blocks (plan_steps)
-    struct Step {
-        bool diag;
-        std::vector<int> subs;
-    };
-    std::vector<Step> steps;
+    std::vector<PassStep> steps;  // plan_steps
 };
-
-// Steps of a kernel pass.  Blocks that hold phase gates only, of at most two
-// tile qubits each, and that the blocks between them allow to meet (they are
-// diagonal too or share no tile qubit) may run as one diagonal step: complex64,
-// where it costs about 1.4 split blocks or one FP32 block, and if the pass gains
-// more than a fifth by it.  A split pass then runs the kernel that splits its
-// matrices itself, about a quarter slower per block (29-qubit QFT: passes of 14,
-// 14 and 9 blocks become 7, 4 and 5 steps, 6.0 + 4.8 + 3.4 against 3.6 + 2.1 +
-// 2.7 ms; at 8 blocks against 7 steps it lost 3.72 to 3.86 ms).
-static void plan_steps(PassWork &w, const std::vector<Block> &gates, int dtype)
-{
-    const int nsub = int(w.subs.size());
-    w.steps.clear();
-    std::vector<PassWork::Step> steps;
-    std::vector<uint64_t> acts;  // tile qubits of each step
-    int rows = 0, blocks = 0, diags = 0;
-    bool terms = false, merged = false;
-    for (int i = 0; i < nsub; ++i) {
-        bool diag = dtype == SV_C64;
-        uint64_t act = w.subs[size_t(i)].qmask & w.qmask;
-        const std::vector<int> *lists[3] = {&w.subs[size_t(i)].members, &w.front[size_t(i)], &w.back[size_t(i)]};
-        for (const std::vector<int> *l : lists)
-            for (int m : *l) {
-                const uint64_t q = qubit_mask(gates[size_t(m)]);
-                act |= q & w.qmask;
-                diag = diag && is_phase_gate(gates[size_t(m)]) && (q & ~(w.qmask | w.omask)) == 0 &&
-                       __builtin_popcountll(q & w.qmask) <= 2;
-            }
-        terms = terms || !w.front[size_t(i)].empty() || !w.back[size_t(i)].empty();
-        if (diag) {
-            int at = -1;  // the diagonal step it can move back to
-            for (int s = int(steps.size()) - 1; s >= 0; --s) {
-                if (steps[size_t(s)].diag) {
-                    at = s;
-                    continue;
-                }
-                if (acts[size_t(s)] & act)
-                    break;
-            }
-            if (at >= 0) {
-                // the latest one reached that it may join; any will do
-                steps[size_t(at)].subs.push_back(i);
-                acts[size_t(at)] |= act;
-                merged = true;
-                continue;
-            }
-        }
-        steps.push_back(PassWork::Step{diag, {i}});
-        acts.push_back(act);
-    }
-    // a diagonal step moves on to the next one where the blocks between allow it
-    for (size_t s = 0; s < steps.size(); ++s) {
-        if (!steps[s].diag)
-            continue;
-        for (size_t t = s + 1; t < steps.size(); ++t) {
-            if (!steps[t].diag) {
-                if (acts[t] & acts[s])
-                    break;
-                continue;
-            }
-            steps[t].subs.insert(steps[t].subs.begin(), steps[s].subs.begin(), steps[s].subs.end());
-            acts[t] |= acts[s];
-            steps.erase(steps.begin() + ptrdiff_t(s));
-            acts.erase(acts.begin() + ptrdiff_t(s));
-            merged = true;
-            --s;
-            break;
-        }
-    }
-    for (const PassWork::Step &s : steps) {
-        if (s.diag && s.subs.size() > 1) {
-            ++diags;
-            rows += kDiagRows;
-            continue;
-        }
-        ++blocks;
-        rows += w.front[size_t(s.subs[0])].empty() && w.back[size_t(s.subs[0])].empty() ? 0 : 1;
-    }
-    const double own = w.split ? 1.25 : 1.0, step = w.split ? 1.4 : 1.0;
-    if (merged && rows <= kMaxTermBlocks && blocks * own + diags * step < 0.8 * nsub * (terms ? own : 1.0)) {
-        w.steps = steps;
-        for (PassWork::Step &s : w.steps)
-            s.diag = s.diag && s.subs.size() > 1;
-        return;
-    }
-    for (int i = 0; i < nsub; ++i)
-        w.steps.push_back(PassWork::Step{false, {i}});
-}
 
 // Monomials of a phase gate's angle: a diagonal gate on qubits Q (targets,
 // then controls) multiplies basis state x by exp(i f(x)), f(x) = arg U[x_t]
@@ -1106,23 +1012,7 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
     pr.rec.highest_target = hi;
     pr.rec.num_gates = w.ngates;
     pr.rec.bytes = 2.0 * double(h->bytes);
-    // every block a dense 16 x 16 complex matrix: 8 * 16 - 2 flops per
-    // amplitude; on the matrix cores three real products of 2 * 16 flops
-    // per amplitude each (FP32 / FP64), or with split BF16 operands two
-    // real output rows x 32 terms x six part products x 2 flops (BF16)
-    // a diagonal step is one complex product per amplitude
-    size_t ndiag = 0;
-    for (const PassWork::Step &s : w.steps)
-        ndiag += s.diag ? 1 : 0;
-    pr.rec.flops = (double(nsub - ndiag) * (8.0 * 16.0 - 2.0) + double(ndiag) * 6.0) * std::ldexp(1.0, h->n);
-    pr.rec.mfma_flops = double(nsub - ndiag) * (w.split ? 768.0 : 96.0) * std::ldexp(1.0, h->n);
-    pr.rec.precision = w.split ? SV_PREC_BF16X6 : SV_PREC_NATIVE;
-    pr.rec.blocks = int(nsub);
-    for (const PassWork::Step &s : w.steps) {
-        const size_t i = size_t(s.subs[0]);
-        pr.rec.term_blocks += (s.diag || !w.front[i].empty() || !w.back[i].empty()) ? 1 : 0;
-        pr.rec.variant_blocks += !s.diag && w.vq[i] != 0 ? 1 : 0;
-    }
+    count_steps(pr.rec, h->n, w, w.steps, w.split);
     pr.rec.tile_log = T;
     for (int b = 0; b < T; ++b)
         pr.rec.tile_mask |= uint64_t(1) << tb[b];
@@ -1173,9 +1063,9 @@ int run_pass_plan(sv_state *h, const std::vector<Block> &gates, const std::vecto
         w.split = precision == SV_PREC_BF16X6 && h->dtype == SV_C64;
         w.off = total;
         if (w.kernel) {
-            plan_steps(w, gates, h->dtype);
+            w.steps = plan_steps(w, gates, h->dtype, w.split);
             uint64_t nmat = 0;
-            for (const PassWork::Step &s : w.steps)
+            for (const PassStep &s : w.steps)
                 for (int sub : s.subs) {
                     const size_t j = size_t(sub);
                     w.nterm_max += uint64_t(1 << kMaxPhaseQubits) * (w.front[j].size() + w.back[j].size() +

@@ -397,7 +397,8 @@ static sv_sweep_record group_record(int n, int dtype, int precision, const std::
     return block_record(n, dtype, b, precision);
 }
 
-sv_sweep_record pass_record(int n, int dtype, int precision, const PassGroup &w, const int *phys, int T)
+sv_sweep_record pass_record(int n, int dtype, int precision, const std::vector<Block> &gates, const PassGroup &w,
+                            const int *phys, int T)
 {
     sv_sweep_record r{};
     r.kind = SV_SWEEP_PASS;
@@ -415,14 +416,7 @@ sv_sweep_record pass_record(int n, int dtype, int precision, const PassGroup &w,
     const double amps = std::ldexp(1.0, n);
     const bool split = dtype == SV_C64 && precision == SV_PREC_BF16X6;
     r.bytes = 2.0 * (dtype == SV_C64 ? 8.0 : 16.0) * amps;
-    r.blocks = int(w.subs.size());
-    r.flops = double(r.blocks) * 126.0 * amps;
-    r.mfma_flops = double(r.blocks) * (split ? 768.0 : 96.0) * amps;
-    r.precision = split ? SV_PREC_BF16X6 : SV_PREC_NATIVE;
-    for (size_t i = 0; i < w.subs.size(); ++i) {
-        r.term_blocks += (!w.front[i].empty() || !w.back[i].empty()) ? 1 : 0;
-        r.variant_blocks += w.vq[i] != 0 ? 1 : 0;
-    }
+    count_steps(r, n, w, plan_steps(w, gates, dtype, split), split);
     int tb[16];
     if (pass_tile_bits(n, T, pm, avoid, tb) == T) {
         r.tile_log = T;
@@ -493,7 +487,7 @@ static PlanRows plan_rows(Ranker &rk, int precision, const std::vector<Block> &g
         std::vector<int> rows, tiles;
         if (w.kernel) {
             for (int o = 0; o < nopt; ++o) {
-                const sv_sweep_record r = pass_record(rk.n, rk.dtype, precision, w, phys, opts[o]);
+                const sv_sweep_record r = pass_record(rk.n, rk.dtype, precision, gates, w, phys, opts[o]);
                 if (r.tile_log == 0)
                     continue;  // the pass does not fit this tile
                 rows.push_back(rk.add(r));

@@ -98,6 +98,15 @@ struct PassGroup {
     int ngates = 0;
     int tile_log = 0;  // kernel pass: LDS tile width chosen by the planner (0: by its blocks)
 };
+// One step of the pass kernel: a block, or a diagonal step for all the phase
+// gates of several blocks.
+struct PassStep {
+    bool diag;
+    std::vector<int> subs;  // the pass's blocks
+};
+// Steps of a kernel pass as it runs (split: with split BF16 products) and as the
+// learned planner counts them.
+std::vector<PassStep> plan_steps(const PassGroup &w, const std::vector<Block> &gates, int dtype, bool split);
 // Runs of gates on one qubit pair whose product is diagonal (CX RZ CX =
 // exp(-i theta/2 Z Z)) become one phase gate, placed at the run's first gate
 // (the gates skipped over act on other qubits and commute with the run), so
@@ -147,8 +156,12 @@ uint64_t costmodel_version(const sv_costmodel *m);
 int learned_pass_plan(sv_costmodel *m, int n, int dtype, int precision, const std::vector<Block> &gates,
                       int max_fused, const int *phys, int orders, std::vector<PassGroup> &plan, double *pred_ms);
 // The sweep record a kernel pass of a plan would produce (physical tile bits
-// from phys), for the tile width T.
-sv_sweep_record pass_record(int n, int dtype, int precision, const PassGroup &w, const int *phys, int T);
+// from phys), for the tile width T; gates: the list the plan was made for.
+sv_sweep_record pass_record(int n, int dtype, int precision, const std::vector<Block> &gates, const PassGroup &w,
+                            const int *phys, int T);
+// The part of a kernel pass's record that its steps give: operations, blocks
+// (diagonal steps among them), blocks with per-tile phases and with variants.
+void count_steps(sv_sweep_record &r, int n, const PassGroup &w, const std::vector<PassStep> &steps, bool split);
 
 // ---------------------------------------------------------------------------
 // Kernel launchers (device code in the .hip sources).  All pointers are

@@ -1238,6 +1238,114 @@ std::vector<std::vector<PassGroup>> pass_plan_candidates(const std::vector<Block
     return cands;
 }
 
+// Steps of a kernel pass.  Blocks that hold phase gates only, of at most two
+// tile qubits each, and that the blocks between them allow to meet (they are
+// diagonal too or share no tile qubit) may run as one diagonal step: complex64,
+// where it costs about 1.4 split blocks or one FP32 block, and if the pass gains
+// more than a fifth by it.  A split pass then runs the kernel that splits its
+// matrices itself, about a quarter slower per block (29-qubit QFT: passes of 14,
+// 14 and 9 blocks become 7, 4 and 5 steps, 6.0 + 4.8 + 3.4 against 3.6 + 2.1 +
+// 2.7 ms; at 8 blocks against 7 steps it lost 3.72 to 3.86 ms).
+std::vector<PassStep> plan_steps(const PassGroup &w, const std::vector<Block> &gates, int dtype, bool split)
+{
+    const int nsub = int(w.subs.size());
+    std::vector<PassStep> steps;
+    std::vector<uint64_t> acts;  // tile qubits of each step
+    int rows = 0, blocks = 0, diags = 0;
+    bool terms = false, merged = false;
+    for (int i = 0; i < nsub; ++i) {
+        bool diag = dtype == SV_C64;
+        uint64_t act = w.subs[size_t(i)].qmask & w.qmask;
+        const std::vector<int> *lists[3] = {&w.subs[size_t(i)].members, &w.front[size_t(i)], &w.back[size_t(i)]};
+        for (const std::vector<int> *l : lists)
+            for (int m : *l) {
+                const uint64_t q = qubit_mask(gates[size_t(m)]);
+                act |= q & w.qmask;
+                diag = diag && is_phase_gate(gates[size_t(m)]) && (q & ~(w.qmask | w.omask)) == 0 &&
+                       __builtin_popcountll(q & w.qmask) <= 2;
+            }
+        terms = terms || !w.front[size_t(i)].empty() || !w.back[size_t(i)].empty();
+        if (diag) {
+            int at = -1;  // the diagonal step it can move back to
+            for (int s = int(steps.size()) - 1; s >= 0; --s) {
+                if (steps[size_t(s)].diag) {
+                    at = s;
+                    continue;
+                }
+                if (acts[size_t(s)] & act)
+                    break;
+            }
+            if (at >= 0) {
+                // the latest one reached that it may join; any will do
+                steps[size_t(at)].subs.push_back(i);
+                acts[size_t(at)] |= act;
+                merged = true;
+                continue;
+            }
+        }
+        steps.push_back(PassStep{diag, {i}});
+        acts.push_back(act);
+    }
+    // a diagonal step moves on to the next one where the blocks between allow it
+    for (size_t s = 0; s < steps.size(); ++s) {
+        if (!steps[s].diag)
+            continue;
+        for (size_t t = s + 1; t < steps.size(); ++t) {
+            if (!steps[t].diag) {
+                if (acts[t] & acts[s])
+                    break;
+                continue;
+            }
+            steps[t].subs.insert(steps[t].subs.begin(), steps[s].subs.begin(), steps[s].subs.end());
+            acts[t] |= acts[s];
+            steps.erase(steps.begin() + ptrdiff_t(s));
+            acts.erase(acts.begin() + ptrdiff_t(s));
+            merged = true;
+            --s;
+            break;
+        }
+    }
+    for (const PassStep &s : steps) {
+        if (s.diag && s.subs.size() > 1) {
+            ++diags;
+            rows += kDiagRows;
+            continue;
+        }
+        ++blocks;
+        rows += w.front[size_t(s.subs[0])].empty() && w.back[size_t(s.subs[0])].empty() ? 0 : 1;
+    }
+    const double own = split ? 1.25 : 1.0, step = split ? 1.4 : 1.0;
+    if (merged && rows <= kMaxTermBlocks && blocks * own + diags * step < 0.8 * nsub * (terms ? own : 1.0)) {
+        for (PassStep &s : steps)
+            s.diag = s.diag && s.subs.size() > 1;
+        return steps;
+    }
+    steps.clear();
+    for (int i = 0; i < nsub; ++i)
+        steps.push_back(PassStep{false, {i}});
+    return steps;
+}
+
+// Every block is a dense 16 x 16 complex matrix: 8 * 16 - 2 flops per amplitude;
+// on the matrix cores three real products of 2 * 16 flops per amplitude each
+// (FP32 / FP64), or with split BF16 operands two real output rows x 32 terms x
+// six part products x 2 flops (BF16).  A diagonal step is one complex product
+// per amplitude.
+void count_steps(sv_sweep_record &r, int n, const PassGroup &w, const std::vector<PassStep> &steps, bool split)
+{
+    int diag = 0;
+    for (const PassStep &s : steps) {
+        const size_t i = size_t(s.subs[0]);
+        diag += s.diag ? 1 : 0;
+        r.term_blocks += s.diag || !w.front[i].empty() || !w.back[i].empty() ? 1 : 0;
+        r.variant_blocks += !s.diag && w.vq[i] != 0 ? 1 : 0;
+    }
+    r.blocks = int(steps.size());
+    r.flops = (double(r.blocks - diag) * (8.0 * 16.0 - 2.0) + double(diag) * 6.0) * std::ldexp(1.0, n);
+    r.mfma_flops = double(r.blocks - diag) * (split ? 768.0 : 96.0) * std::ldexp(1.0, n);
+    r.precision = split ? SV_PREC_BF16X6 : SV_PREC_NATIVE;
+}
+
 std::vector<PassGroup> plan_passes(const std::vector<Block> &gates, int pass_qubits, int max_fused, int n, int T0,
                                    const int *phys, int orders)
 {

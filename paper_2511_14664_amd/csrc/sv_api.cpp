@@ -805,6 +805,14 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
                 tt[nt] = t;
             ++nt;
         };
+        // The step's terms, merged.  Complex64 kernels add the high 32 bits of
+        // a turn: half a unit of them is added here, so that they round it.
+        auto end_terms = [&]() {
+            if (h->dtype == SV_C64)
+                for (uint64_t e = first; e < nt; ++e)
+                    tt[e].turn += uint64_t(1) << 31;
+            return uint32_t(nt - first);
+        };
         for (size_t si = 0; si < nsub; ++si) {
             if (w.steps[si].diag) {
                 PassSub d{};
@@ -844,7 +852,7 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
                     set_error("pass %zu: phase term table overflow", index);
                     return SV_EINVAL;
                 }
-                d.nterm = uint32_t(nt - first);
+                d.nterm = end_terms();
                 desc[si] = d;
                 continue;
             }
@@ -974,7 +982,7 @@ int stage_launch_pass(sv_state *h, const std::vector<Block> &gates, const PassWo
                         return SV_EINVAL;
                     }
                 }
-            d.nterm = uint32_t(nt - first);
+            d.nterm = end_terms();
             if (d.nterm > 0) {
                 if (pslot >= uint32_t(kMaxTermBlocks)) {
                     set_error("pass %zu: more than %d blocks with phase terms", index, kMaxTermBlocks);

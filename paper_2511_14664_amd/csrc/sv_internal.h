@@ -271,7 +271,8 @@ static_assert(sizeof(PassSub) == 96, "pass block descriptor layout");
 // omask (physical bits), entry (r, c) of the block matrix gains the angle
 // 2 pi turn / 2^64 if the block-local column index c (front) or row index r
 // (back) covers smask.  Angles in fixed-point turns add exactly and wrap
-// modulo 2 pi by themselves.
+// modulo 2 pi by themselves.  Complex64 kernels add the high 32 bits (half a
+// unit of them is part of turn).
 struct PassTerm {
     uint64_t omask;
     uint32_t smask;

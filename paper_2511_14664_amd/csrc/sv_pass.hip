@@ -152,7 +152,8 @@ __device__ __forceinline__ void lds_add(uint64_t *p, uint64_t v)
 
 // Diagonal step of a complex64 tile: amplitude x times exp(2 pi i f(x)), f a
 // constant, one coefficient per tile bit and one per pair of bits (row: fixed
-// point turns at diag_entry()), summed exactly.  The angles of a thread's
+// point turns at diag_entry()); their sums are exact, each term of the pass was
+// rounded to 2^-32 turns (error at most 7e-10 rad).  The angles of a thread's
 // amplitudes start from the sum over its thread bits and grow by one addition
 // each over the bits its accesses differ in; then a sine and a cosine and one
 // complex product per amplitude, on the vector unit.  About 1.4 split blocks or
@@ -262,9 +263,10 @@ void k_pass(R *__restrict__ st, const TileArgs a, const PassSub *__restrict__ su
     // Per-tile phase angles of the blocks carrying phase terms, in an LDS
     // table: row pslot holds the 16 column angles (front terms) and the 16
     // row angles (back terms) of that block on this tile, in fixed-point
-    // turns (exact sums wrapping mod 2 pi: 32 bits for complex64, 64 for
-    // complex128).  Wave w fills the rows of term blocks w, w + NW, ...: its
-    // lanes take the block's monomials e = lane, lane + 64, ... and each one
+    // turns (exact sums wrapping mod 2 pi: 32 bits for complex64, to which
+    // the terms come rounded, 64 for complex128).  Wave w fills the rows of
+    // term blocks w, w + NW, ...: its lanes take the block's monomials
+    // e = lane, lane + 64, ... and each one
     // whose outer bits this tile has adds its turn to the row's (side, slot
     // mask) entry with an LDS atomic add (integer sums: the same in any
     // order); a subset sum over the four mask bits across lanes then gives

@@ -15,6 +15,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <numeric>
 #include <thread>
 #include <vector>
 
@@ -275,29 +276,29 @@ void cut_runs(int lp, std::vector<BStep> &steps, std::vector<StepPlan> &plans, s
               std::vector<BRun> &runs)
 {
     const int nr = lp - kBatchThreadLog;
+    const size_t count = steps.size() - first;
     auto bits_of = [](const BStep &s) { return 1u << s.a | (s.type != 0 ? 1u << s.b : 0u); };
-    std::vector<BStep> left(steps.begin() + ptrdiff_t(first), steps.end());
-    std::vector<StepPlan> pleft(plans.begin() + ptrdiff_t(first), plans.end());
-    steps.resize(first);
-    plans.erase(plans.begin() + ptrdiff_t(first), plans.end());
+    std::vector<uint32_t> left(count), order;  // by position behind first
+    std::iota(left.begin(), left.end(), 0u);
+    order.reserve(count);
     while (!left.empty()) {
         uint32_t set = 0, blocked = 0;
-        BRun run{};
-        run.step0 = int32_t(steps.size());
-        std::vector<BStep> rest;
-        std::vector<StepPlan> prest;
-        for (size_t k = 0; k < left.size(); ++k) {
-            const uint32_t m = bits_of(left[k]);
+        const size_t start = order.size();
+        size_t rest = 0;
+        for (const uint32_t k : left) {
+            const uint32_t m = bits_of(steps[first + k]);
             if ((m & blocked) == 0 && __builtin_popcount(set | m) <= nr) {
                 set |= m;
-                steps.push_back(left[k]);
-                plans.push_back(pleft[k]);
+                order.push_back(k);
             } else {
                 blocked |= m;
-                rest.push_back(left[k]);
-                prest.push_back(pleft[k]);
+                left[rest++] = k;
             }
         }
+        left.resize(rest);
+        BRun run{};
+        run.step0 = int32_t(first + start);
+        run.nsteps = int32_t(order.size() - start);
         for (int x = 0; x < lp && __builtin_popcount(set) < nr; ++x)
             set |= 1u << x;
         int bit_of[kBatchMaxTileLog], n = 0;
@@ -321,21 +322,28 @@ void cut_runs(int lp, std::vector<BStep> &steps, std::vector<StepPlan> &plans, s
         for (int x = 0; x < lp; ++x)
             if (!(((set | lanes) >> x) & 1))
                 run.lane[n++] = uint8_t(x);
-        run.nsteps = int32_t(steps.size()) - run.step0;
-        for (int k = run.step0; k < run.step0 + run.nsteps; ++k) {
-            BStep &s = steps[size_t(k)];
+        for (size_t e = start; e < order.size(); ++e) {
+            BStep &s = steps[first + order[e]];
             s.a = uint8_t(bit_of[s.a]);
             if (s.type != 0)
                 s.b = uint8_t(bit_of[s.b]);
             if (s.type == 2 && s.a > s.b) {
                 std::swap(s.a, s.b);
-                plans[size_t(k)].swap = true;
+                plans[first + order[e]].swap = true;
             }
         }
         runs.push_back(run);
-        left.swap(rest);
-        pleft.swap(prest);
     }
+    std::vector<BStep> in_order;
+    std::vector<StepPlan> plans_in_order;
+    in_order.reserve(count);
+    plans_in_order.reserve(count);
+    for (const uint32_t k : order) {
+        in_order.push_back(steps[first + k]);
+        plans_in_order.push_back(std::move(plans[first + k]));
+    }
+    std::copy(in_order.begin(), in_order.end(), steps.begin() + ptrdiff_t(first));
+    std::move(plans_in_order.begin(), plans_in_order.end(), plans.begin() + ptrdiff_t(first));
 }
 
 int build(sv_batch *b)

@@ -803,10 +803,13 @@ __global__ __launch_bounds__(kPrepThreads) void k_sample_prep(const double *__re
         cnz[tid] = nz;
     }
     __syncthreads();
-    if (tid < NG) {
+    // groups, and chunks of this thread's group, that there are (few states of
+    // many qubits fill them: the sums are chains of LDS reads)
+    const int ng = int((nchunk + kPrepGroup - 1) / kPrepGroup), in_group = nchunk < kPrepGroup ? int(nchunk) : kPrepGroup;
+    if (tid < ng) {
         double run = 0.0;
         int64_t last = -1;
-        for (int c = 0; c < kPrepGroup; ++c) {
+        for (int c = 0; c < in_group; ++c) {
             run += csum[tid * kPrepGroup + c];
             last = cnz[tid * kPrepGroup + c] >= 0 ? cnz[tid * kPrepGroup + c] : last;
         }
@@ -817,27 +820,27 @@ __global__ __launch_bounds__(kPrepThreads) void k_sample_prep(const double *__re
     if (tid == 0) {
         double run = 0.0;
         int64_t last = 0;
-        for (int c = 0; c < NG; ++c) {
+        for (int c = 0; c < ng; ++c) {
             gpre[c] = run;
             run += gsum[c];
             last = gnz[c] >= 0 ? gnz[c] : last;
         }
-        gpre[NG] = run;
+        gpre[ng] = run;
         s_last = last;
     }
     __syncthreads();
-    if (tid < NG) {
+    if (tid < ng) {
         const double start = gpre[tid];
         double part = 0.0;
-        for (int c = 0; c < kPrepGroup; ++c) {
+        for (int c = 0; c < in_group; ++c) {
             cpre[tid * kPrepGroup + c] = start + part;
             part += csum[tid * kPrepGroup + c];
         }
-        if (tid == NG - 1)
-            cpre[kPrepThreads] = gpre[NG];
+        if (tid == ng - 1)
+            cpre[nchunk] = gpre[ng];
     }
     __syncthreads();
-    const double norm = cpre[kPrepThreads];
+    const double norm = cpre[nchunk];
     for (int sh = tid; sh < shots; sh += kPrepThreads) {
         const double t = uni[sh] * norm;
         uint64_t lo = 0, hi = nchunk;  // first chunk c with cpre[c + 1] > t
@@ -877,22 +880,28 @@ __global__ __launch_bounds__(kPrepThreads) void k_sample_prep(const double *__re
 }
 
 // Stage 2: one workgroup per shot.  The sums of the block's segments of 1024
-// amplitudes, 4 waves each taking every fourth segment with its loads in
-// flight together, name the segment to start in; from there the block is
-// walked in segments (4 consecutive amplitudes per thread) to the first
+// amplitudes, ROUND segments at a time with their loads in flight together (0:
+// the block is one segment), name the segment to start in; from there the block
+// is walked in segments (4 consecutive amplitudes per thread) to the first
 // amplitude of nonzero probability whose in-block running sum exceeds the
 // residual target.  If rounding leaves none, the last index of nonzero
 // probability seen is returned.  (Walking from the block's start, each segment
 // waits for memory: 73 us for 1000 shots in 2^14-amplitude blocks at 28 qubits,
-// against 31.)
+// against 31 with eight segments at a time.  Many shots are bound by the bytes
+// read: a million at 24 qubits complex128 take 25 ms with four segments at a
+// time, 30 with eight, 39 where every segment is summed, 28 by the walk.)  Many
+// shots want eight wavefronts per SIMD (with 84 registers a million of an
+// 8-qubit complex128 state took 5.6 ms instead of 4.5), few the registers for
+// their loads (1000 at 20 qubits complex64: 47 us, 60 with 64 registers).
 constexpr int kSearchSegLog = 10;
 constexpr int kSearchMaxLog = 16;
+constexpr int kSearchMany = 4096;  // shots that keep every CU's memory pipes busy
 
-template <typename R>
-__global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict__ st,
-                                                            const int64_t *__restrict__ blocks,
-                                                            const double *__restrict__ targets,
-                                                            int64_t *__restrict__ out, int lbs)
+template <typename R, int ROUND>
+__global__ __launch_bounds__(kThreads, ROUND == 8 ? 4 : 8) void k_sample_search(const R *__restrict__ st,
+                                                               const int64_t *__restrict__ blocks,
+                                                               const double *__restrict__ targets,
+                                                               int64_t *__restrict__ out, int lbs)
 {
     using C = typename CT<R>::C;
     constexpr int SEG = 1 << kSearchSegLog;
@@ -913,40 +922,45 @@ __global__ __launch_bounds__(kThreads) void k_sample_search(const R *__restrict_
     }
     double running = 0.0;
     int seg0 = 0;
-    if (bsz > SEG) {
+    if constexpr (ROUND > 0) {
+        // ROUND segments at a time, up to the first whose end passes the target,
+        // else the last of nonzero sum
         const int nseg = bsz >> kSearchSegLog;
-        for (int g = w; g < nseg; g += 8) {
-            const C *va = v + base + (uint64_t(g) << kSearchSegLog);
-            const bool two = g + 4 < nseg;
-            const C *vb = two ? va + 4 * SEG : va;
-            double sa = 0.0, sb = 0.0;
-#pragma unroll
-            for (int k = 0; k < SEG / 64; ++k) {
-                sa += prob(va[k * 64 + lane]);
-                sb += prob(vb[k * 64 + lane]);
-            }
-            sa = wave_sum(sa);
-            sb = wave_sum(sb);
-            if (lane == 0) {
-                ssum[g] = sa;
-                if (two)
-                    ssum[g + 4] = sb;
-            }
-        }
-        __syncthreads();
-        // the first segment whose end passes the target, else the last of
-        // nonzero sum
         int last = 0;
         double before = 0.0, lastbefore = 0.0;
         bool hit = false;
-        for (int g = 0; g < nseg && !hit; ++g) {
-            const double x = ssum[g];
-            if (x > 0.0) {
-                last = g;
-                lastbefore = before;
+        for (int g0 = 0; g0 < nseg && !hit; g0 += ROUND) {
+            const int g = g0 + w;
+            if (g < nseg) {
+                const C *va = v + base + (uint64_t(g) << kSearchSegLog);
+                const bool two = ROUND > 4 && g + 4 < nseg;
+                const C *vb = two ? va + 4 * SEG : va;
+                double sa = 0.0, sb = 0.0;
+#pragma unroll
+                for (int k = 0; k < SEG / 64; ++k) {
+                    sa += prob(va[k * 64 + lane]);
+                    if constexpr (ROUND > 4)
+                        sb += prob(vb[k * 64 + lane]);
+                }
+                sa = wave_sum(sa);
+                if constexpr (ROUND > 4)
+                    sb = wave_sum(sb);
+                if (lane == 0) {
+                    ssum[g] = sa;
+                    if (two)
+                        ssum[g + 4] = sb;
+                }
             }
-            before += x;
-            hit = before > target;
+            __syncthreads();
+            for (int i = g0; i < nseg && i < g0 + ROUND && !hit; ++i) {
+                const double x = ssum[i];
+                if (x > 0.0) {
+                    last = i;
+                    lastbefore = before;
+                }
+                before += x;
+                hit = before > target;
+            }
         }
         seg0 = last << kSearchSegLog;
         running = lastbefore;
@@ -1753,12 +1767,20 @@ hipError_t launch_sample_search(const void *st, int n, int dtype, const int64_t 
 {
     if (shots <= 0 || lbs < 1 || lbs > n || lbs > kSearchMaxLog)
         return hipSuccess;
-    if (dtype == SV_C64)
-        hipLaunchKernelGGL(k_sample_search<float>, dim3(shots), dim3(kThreads), 0, s, (const float *)st, d_blocks,
-                           d_targets, d_out, lbs);
+    auto launch = [&](auto r_tag, auto round_tag) {
+        using R = decltype(r_tag);
+        hipLaunchKernelGGL((k_sample_search<R, decltype(round_tag)::value>), dim3(shots), dim3(kThreads), 0, s,
+                           (const R *)st, d_blocks, d_targets, d_out, lbs);
+    };
+    auto launch_r = [&](auto round_tag) {
+        dtype == SV_C64 ? launch(float{}, round_tag) : launch(double{}, round_tag);
+    };
+    if (lbs <= kSearchSegLog)
+        launch_r(std::integral_constant<int, 0>{});
+    else if (shots < kSearchMany)
+        launch_r(std::integral_constant<int, 8>{});
     else
-        hipLaunchKernelGGL(k_sample_search<double>, dim3(shots), dim3(kThreads), 0, s, (const double *)st, d_blocks,
-                           d_targets, d_out, lbs);
+        launch_r(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }
 

@@ -1356,7 +1356,8 @@ struct MargRoute {
 constexpr uint64_t kMaxFolded = uint64_t(1) << 26;  // doubles
 constexpr int kFoldGrid = 12;  // log2 workgroups of a fold, where the bins leave enough bits
 
-// The fold route (n >= kSegLog + 2, at most 10 bins below bit 12): as many
+// The fold route (n >= kSegLog + 2, or kSegLog where no bin is below bit 12; at
+// most 10 such bins): as many
 // fold bits as bring the workgroups down to 2^kFoldGrid, so that their partial
 // sums stay small against the read.
 MargRoute fold_route(int n, int m, const int *phys_q)
@@ -1395,9 +1396,9 @@ MargRoute fold_route(int n, int m, const int *phys_q)
                                       : lb + q - kSegLog - __builtin_popcountll(r.fold.foldmask & below);
     }
     r.p2 = marg_plan(n2, m);
-    if (!r.p2.rmajor && m <= 15) {
-        // few rest entries per bin: still one workgroup per bin (a thread per
-        // bin would leave the GPU nearly empty for up to 2^15 bins)
+    if (!r.p2.rmajor && m <= 15 && n2 > m) {
+        // few rest entries per bin, but not one: still one workgroup per bin (a
+        // thread per bin would leave the GPU nearly empty for up to 2^15 bins)
         r.p2.rmajor = true;
         r.p2.chunks = 1;
         r.p2.per_chunk = uint64_t(1) << (n2 - m);
@@ -1411,7 +1412,7 @@ MargRoute marg_route(int n, int m, const int *phys_q)
     int lb = 0;
     for (int b = 0; b < m; ++b)
         lb += phys_q[b] < kSegLog ? 1 : 0;
-    if (n >= kSegLog + 2 && lb <= 10) {
+    if (n >= kSegLog + (lb > 0 ? 2 : 0) && lb <= 10) {
         MargRoute r = fold_route(n, m, phys_q);
         if (r.red <= kMaxFolded)
             return r;
@@ -1467,10 +1468,12 @@ hipError_t launch_marginal(const void *st, int n, int dtype, const int *phys_q, 
         a2.per_chunk = route.p2.per_chunk;
         const double *red = d_scratch;
         if (route.p2.rmajor) {
-            double *part = d_scratch + route.red;
+            // (the launch that adds up one chunk: 3 us of a call that takes 20 on
+            // small states)
+            double *part = a2.chunks == 1 ? d_out : d_scratch + route.red;
             hipLaunchKernelGGL(k_marg_rmajor_d, dim3(a2.chunks, a2.nbins), dim3(kThreads), 0, s, red, part, a2);
             e = hipGetLastError();
-            if (e != hipSuccess)
+            if (e != hipSuccess || a2.chunks == 1)
                 return e;
             return launch_sum_rows(part, d_out, uint64_t(a2.nbins), a2.chunks, s);
         } else {

@@ -1663,7 +1663,11 @@ hipError_t launch_expect_multi(const void *st, int n, int dtype, const uint64_t 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || chunks == 1)
         return e;
-    return launch_sum_rows(d_scratch, d_out, uint64_t(nt), uint32_t(chunks), s);
+    if (chunks < 32)
+        return launch_sum_rows(d_scratch, d_out, uint64_t(nt), uint32_t(chunks), s);
+    // (one thread adding up 128 partial sums: 4 us of a call of 28)
+    hipLaunchKernelGGL(k_sum_rows_wide, dim3(uint32_t(nt)), dim3(kThreads), 0, s, d_scratch, d_out, uint32_t(chunks));
+    return hipGetLastError();
 }
 
 // Workgroups of a persistent expectation sweep over nw work items.

@@ -441,7 +441,7 @@ int run_blocks(sv_state *h, const std::vector<Block> &blocks_in, int precision, 
 // (the program is read from memory that later calls reuse, while the
 // launches' arguments are part of the graph) and the BF16X3 arithmetic.
 // A state of 64 KiB takes longer to come and go through one CU than the
-// launches of two gates (8.5 against 7.0 us; three steps 9.4 against 11).
+// launches of two gates (8.5 against 7.8 us; three steps 9.8 against 11.1).
 bool small_route(sv_state *h, size_t nsteps, int precision)
 {
     if (nsteps < (h->bytes >= 65536 ? 3 : 2) || !small_fits(h->n, h->dtype) || h->profiling ||

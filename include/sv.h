@@ -146,7 +146,9 @@ typedef struct sv_run_stats {
                                    complex64 / 2^12 complex128 amplitudes, steps of one launch that holds
                                    the state in LDS (unless sweeps are being timed or the stream captured) */
     int64_t fused_blocks;       /* sweeps that apply more than one gate */
-    double algorithmic_bytes;   /* HBM bytes the sweeps must move (128-byte lines) */
+    double algorithmic_bytes;   /* HBM bytes the sweeps must move (128-byte lines) if each crosses HBM;
+                                   steps of one launch (see sweeps) share one read and one write of the
+                                   state, so no bandwidth follows from this where they do */
     double flops;               /* real floating-point operations of the sweeps */
 } sv_run_stats;
 

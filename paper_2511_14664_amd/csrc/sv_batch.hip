@@ -11,10 +11,17 @@
 // raises the error flag, every workgroup drains, and the host reports it.
 //
 // Cross-workgroup visibility: whatever another workgroup reads (amplitudes,
-// partial sums) is stored at device scope, past the XCD's L2; every wave waits
-// for its stores to complete, then a barrier, then one atomic increment; a
-// consumer reads the count, passes a barrier, and every thread issues an
-// agent-scope acquire fence before loading.
+// partial sums) is stored at device scope (sc1, what a relaxed agent-scope
+// atomic store compiles to): the store goes through the XCD's L2 to the memory
+// that all XCDs share, and vmcnt counts it until that memory has acknowledged
+// it.  Every wave waits for its count to reach zero, then a barrier, then one
+// thread raises the count of finished tiles, so whoever reads the raised count
+// finds the stores in memory; it passes a barrier, and every thread issues an
+// agent-scope acquire fence (its caches' lines of the tile are dropped) before
+// loading.  An agent-scope release is this same wait and, before it, the write
+// back of L2 lines left dirty by stores of narrower scope; those write nothing
+// that another workgroup of the launch reads (results in `out` are read after
+// the launch).
 #include "sv_batch.h"
 #include "sv_device.h"
 
@@ -62,9 +69,10 @@ __device__ __forceinline__ C &lds_at(unsigned char *tileb, uint32_t o)
     return *reinterpret_cast<C *>(tileb + o);
 }
 
-// This wave's device-scope stores have completed.  (An agent-scope release fence
-// adds a write-back of the whole L2, with no dirty line of ours in it: 9.5
-// against 1.8 us per 2^13 tile.)
+// This wave's device-scope stores are in the memory that all XCDs share (see the
+// top of the file).  An agent-scope release fence adds a write-back of the whole
+// L2, which holds no dirty line that matters here: 9.5 against 1.8 us per 2^13
+// tile.
 __device__ __forceinline__ void publish()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // nothing moves below

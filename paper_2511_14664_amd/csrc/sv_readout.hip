@@ -121,8 +121,9 @@ __device__ __forceinline__ void halve_values(double (&v)[NT], int lane)
 
 // block_sum of NT values at once (a power of two up to 64), the same sums to
 // the bit: each shuffle step hands half of the values still held to the other
-// half of the lanes, 2 NT - 2 shuffles for NT = 32 where one value at a time
-// takes 6 NT.  out(t, sum) is called by one thread for each value.  sh: 4 NT.
+// half of the lanes, NT - 1 + 6 - log2(NT) shuffles of a double (32 for NT = 32)
+// where one value at a time takes 6 NT (192).  out(t, sum) is called by one
+// thread for each value.  sh: 4 NT.
 template <int NT, typename F>
 __device__ __forceinline__ void block_sums(double (&v)[NT], double *sh, F out)
 {

@@ -9,7 +9,7 @@
 // write, so the step records and the matrices are in LDS too, loaded for as
 // many steps at a time as fit beside the state.
 //
-// Measured on MI355X, a circuit per call: 253 gates on 11 qubits complex64
+// Measured on MI355X, a circuit per call: 256 gates on 11 qubits complex64
 // (one sweep per gate) 105 us against 700-1020 us by launches; 29 blocks of up
 // to five qubits on 12 qubits complex128 125 us of kernel against 171 us of
 // kernels and 320-350 us by launches.  A one-target step takes 0.27 us at 8

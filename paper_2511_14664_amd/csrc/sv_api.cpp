@@ -2005,7 +2005,7 @@ int sv_readout(sv_handle h, const int *qubits, int m, double *probs, const char 
     const int lbs = readout_log_block(h->n, mm, phys);
     const uint64_t nb = uint64_t(1) << (h->n - lbs);
     const uint64_t nbins = want_p ? uint64_t(1) << m : 0;
-    const uint64_t red = readout_scratch_doubles(h->n, mm, phys);
+    const uint64_t red = readout_scratch_doubles(h->n, mm, phys, nz);
     // scratch: fold and Z partials | block totals | marginal | Z values | shot work
     const uint64_t need = red + nb + nbins + uint64_t(nz) + kShotWork * uint64_t(shots);
     rc = ensure_scratch(h, need * 8);

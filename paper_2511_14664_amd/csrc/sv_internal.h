@@ -341,7 +341,7 @@ constexpr int kReadoutMaxZ = 32;
 // Possible where readout_fusable; scratch of readout_scratch_doubles.
 bool readout_fusable(int n, int m, const int *phys_q);
 int readout_log_block(int n, int m, const int *phys_q);
-uint64_t readout_scratch_doubles(int n, int m, const int *phys_q);
+uint64_t readout_scratch_doubles(int n, int m, const int *phys_q, int nt);
 hipError_t launch_readout(const void *st, int n, int dtype, const int *phys_q, int m, const uint64_t *zmasks,
                           int nt, double *d_scratch, double *d_marg, double *d_z, double *d_tot, hipStream_t s);
 

@@ -1836,13 +1836,13 @@ int readout_log_block(int n, int m, const int *phys_q)
     return kSegLog + total_log(r.fold);
 }
 
-uint64_t readout_scratch_doubles(int n, int m, const int *phys_q)
+uint64_t readout_scratch_doubles(int n, int m, const int *phys_q, int nt)
 {
     MargRoute r;
     if (!fused_route(n, m, phys_q, r))
         return 0;
     const uint64_t nblk = uint64_t(1) << (n - kSegLog - r.fold.F);
-    return r.scratch + uint64_t(kMaxZ) * nblk;
+    return r.scratch + uint64_t(nt) * nblk;
 }
 
 hipError_t launch_readout(const void *st, int n, int dtype, const int *phys_q, int m, const uint64_t *zmasks,

@@ -272,7 +272,13 @@ void fill_matrices(sv_batch *b)
 // that no step left behind shares a bit with, so each tile bit sees its steps
 // in their order.  Reorders steps and plans alike and rewrites the steps' bits
 // as register bits.
-void cut_runs(int lp, std::vector<BStep> &steps, std::vector<StepPlan> &plans, size_t first,
+// A circuit's first pass starts from one nonzero amplitude, and the rounding of
+// a step is shared by all amplitudes that come of those it acts on, so the steps
+// that spread the state go first: until every bit has been acted on, a run takes
+// only steps that reach a new one, if there are any that it can take.  (Several
+// layers on the first run's five bits alone raised the error of the expectation
+// values of 14- to 16-qubit complex64 circuits by 12 %.)
+void cut_runs(int lp, std::vector<BStep> &steps, std::vector<StepPlan> &plans, size_t first, bool from_zero,
               std::vector<BRun> &runs)
 {
     const int nr = lp - kBatchThreadLog;
@@ -281,14 +287,21 @@ void cut_runs(int lp, std::vector<BStep> &steps, std::vector<StepPlan> &plans, s
     std::vector<uint32_t> left(count), order;  // by position behind first
     std::iota(left.begin(), left.end(), 0u);
     order.reserve(count);
+    uint32_t reached = from_zero ? 0 : ~0u, reachable = 0;
+    for (size_t k = first; k < steps.size(); ++k)
+        reachable |= bits_of(steps[k]);
+    bool spread = true;
     while (!left.empty()) {
+        spread = spread && (reachable & ~reached) != 0;
         uint32_t set = 0, blocked = 0;
         const size_t start = order.size();
         size_t rest = 0;
         for (const uint32_t k : left) {
             const uint32_t m = bits_of(steps[first + k]);
-            if ((m & blocked) == 0 && __builtin_popcount(set | m) <= nr) {
+            if ((m & blocked) == 0 && __builtin_popcount(set | m) <= nr &&
+                (!spread || (m & ~reached) != 0)) {
                 set |= m;
+                reached |= m;
                 order.push_back(k);
             } else {
                 blocked |= m;
@@ -296,6 +309,11 @@ void cut_runs(int lp, std::vector<BStep> &steps, std::vector<StepPlan> &plans, s
             }
         }
         left.resize(rest);
+        if (order.size() == start) {  // none of them: whatever comes next
+            spread = false;
+            continue;
+        }
+        spread = true;
         BRun run{};
         run.step0 = int32_t(first + start);
         run.nsteps = int32_t(order.size() - start);
@@ -437,7 +455,7 @@ int build(sv_batch *b)
             }
             bp.run0 = int32_t(runs.size());
             if (batch_runs(bp.lp))
-                cut_runs(bp.lp, steps, b->steps, size_t(bp.step0), runs);
+                cut_runs(bp.lp, steps, b->steps, size_t(bp.step0), p == 0, runs);
             bp.nruns = int32_t(runs.size()) - bp.run0;
             for (size_t k = size_t(bp.step0); k < steps.size(); ++k) {
                 steps[k].mat = b->steps[k].mat = mat;

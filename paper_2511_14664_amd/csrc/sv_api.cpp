@@ -1684,10 +1684,9 @@ static double pauli_value(double v, int ny)
 // double per string, two (Re, Im) for a string flagged kPair.
 //  - Small states (2^kExpectMultiMax amplitudes, in cache): all strings in one
 //    launch per expect_multi_batch().
-//  - Z strings: up to expect_z_batch() by the sweep that adds each string up
-//    (2^28 complex64 amplitudes, 8 strings: 0.327 ms a call against 0.356 by
-//    the Walsh kernel), more by the Walsh kernel, expect_walsh_batch() per
-//    read (16 strings of 2^24: 47 us against 72 with the adding sweep).
+//  - Z strings: up to expect_z_batch() (8 or 16) by the sweep that adds each
+//    string up, more by the Walsh kernel, expect_walsh_batch() per read (32
+//    strings of 2^24: 47 us against 118 with the adding sweep).
 //  - General strings: as many as share a tile in one read; a string that
 //    shares it with no other by its own sweep over the pairs.
 static int expect_core(sv_state *h, int nterms, const uint64_t *xs, const uint64_t *yzs, const int *nys,
@@ -1730,8 +1729,9 @@ static int expect_core(sv_state *h, int nterms, const uint64_t *xs, const uint64
         }
         nres = size_t(nterms);
     } else {
-        const bool walsh = nz > expect_z_batch();
-        const int zb = std::min(walsh ? expect_walsh_batch() : expect_z_batch(), kB);
+        const int few = expect_z_batch(h->n, h->dtype);
+        const bool walsh = nz > few;
+        const int zb = std::min(walsh ? expect_walsh_batch() : few, kB);
         for (int s = 0; s < nz && rc == SV_OK; s += zb) {
             const int nb = std::min(zb, nz - s);
             gather(s, nb);

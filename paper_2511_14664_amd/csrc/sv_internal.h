@@ -297,7 +297,7 @@ hipError_t launch_pass(void *st, int n, int dtype, int T, const int *tile_bits, 
 // allocation-free read-out on `device`, which must be the current device.
 int noalloc_scratch(int device, double **ptr, uint64_t *doubles);
 // Z strings per launch_expect_z call.
-int expect_z_batch();
+int expect_z_batch(int n, int dtype);
 hipError_t launch_expect_z(const void *st, int n, int dtype, const uint64_t *zmasks, int nt,
                            double *d_scratch, double *d_out, hipStream_t s);
 hipError_t launch_expect_xy(const void *st, int n, int dtype, uint64_t xmask, uint64_t yzmask,

@@ -247,7 +247,7 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Z-string expectations: sum_i |a_i|^2 (-1)^popcount(i & z_t), up to kFewZ
-// strings per pass (more go through the Walsh kernel below).
+// strings per pass (more go through the Walsh kernel below: expect_z_batch()).
 // part[t * gridDim + block].
 //
 // A thread visits the indexes h0 + 256 u + threadIdx.x, u < 16, with h0 a
@@ -263,7 +263,7 @@ namespace {
 // unit, shared by a CU's four SIMDs, otherwise bounds the sweep).
 // ---------------------------------------------------------------------------
 constexpr int kMaxZ = 32;  // strings of one fused read-out
-constexpr int kFewZ = 8;
+constexpr int kFewZ = 16;
 struct ExpZArgs {
     uint64_t nelem;
     int nt;
@@ -1570,15 +1570,21 @@ uint64_t expect_scratch_doubles(int n)
     return uint64_t(kMaxZ) * kExpGrid;
 }
 
-int expect_z_batch()
+// The Walsh kernel's work does not depend on the strings, this sweep's grows
+// with them.  Large complex64 states are read faster by the sweep up to 16
+// strings (9 / 16 strings, by it and by the Walsh kernel: 2^25 63 / 64 and 65 /
+// 66 us, 2^27 174 / 180 and 190, 2^29 631 / 644 and 689); 2^24 amplitudes stay
+// in cache (46 / 47 and 44), and complex128 amplitudes bring half the work a
+// byte (2^27, nine strings: 348 and 333).
+int expect_z_batch(int n, int dtype)
 {
-    return kFewZ;
+    return dtype == SV_C64 && n >= 25 ? kFewZ : 8;
 }
 
 hipError_t launch_expect_z(const void *st, int n, int dtype, const uint64_t *zmasks, int nt, double *d_scratch,
                            double *d_out, hipStream_t s)
 {
-    if (nt < 1 || nt > kFewZ)
+    if (nt < 1 || nt > expect_z_batch(n, dtype))
         return hipErrorInvalidValue;
     ExpZArgs a{};
     a.nelem = uint64_t(1) << n;
@@ -1587,10 +1593,12 @@ hipError_t launch_expect_z(const void *st, int n, int dtype, const uint64_t *zma
         a.z[t] = zmasks[t];
     const uint32_t grid = exp_grid(n);
     const dim3 g(grid), b(kThreads);
-    if (dtype == SV_C64)
-        hipLaunchKernelGGL((k_expect_z<float, kFewZ>), g, b, 0, s, (const float *)st, d_scratch, a);
+    if (dtype == SV_C128)
+        hipLaunchKernelGGL((k_expect_z<double, 8>), g, b, 0, s, (const double *)st, d_scratch, a);
+    else if (nt <= 8)
+        hipLaunchKernelGGL((k_expect_z<float, 8>), g, b, 0, s, (const float *)st, d_scratch, a);
     else
-        hipLaunchKernelGGL((k_expect_z<double, kFewZ>), g, b, 0, s, (const double *)st, d_scratch, a);
+        hipLaunchKernelGGL((k_expect_z<float, kFewZ>), g, b, 0, s, (const float *)st, d_scratch, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;

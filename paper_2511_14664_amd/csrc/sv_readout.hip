@@ -1133,10 +1133,6 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
     const int bin0 = tid / G;
     const bool owner_mode = B >= kThreads;
     f64x16 own = 0.0;  // NR of them used
-    // rest enumeration for the group mode: x_r = deposit(r, restmask), r = gi, gi + G, ...
-    const uint32_t x_first = deposit(uint32_t(gi), restmask);
-    const uint32_t x_step = deposit(uint32_t(G), restmask);
-    const uint32_t d_bin0 = deposit(uint32_t(bin0), a.binmask);
     // Z strings: the lane reports string `lane`'s segment parity by ballot;
     // walsh index of a string: its bits among the loads' varying index bits
     const int lane = tid & 63;
@@ -1237,14 +1233,27 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
             }
         }
     }
-    // thread tid's own[k] is entry 2 tid + 512 (k / 2) + k % 2 (c64) or
-    // tid + 256 k (c128)
+    const bool one_bin = KSUM && a.lb == 0;
+    if (!one_bin) {
+        // thread tid's own[k] is entry 2 tid + 512 (k / 2) + k % 2 (c64) or
+        // tid + 256 k (c128)
 #pragma unroll
-    for (int k = 0; k < NR; ++k)
-        pr[F32 ? 2 * tid + 2 * kThreads * (k >> 1) + (k & 1) : tid + kThreads * k] = own[k];
-    __syncthreads();
+        for (int k = 0; k < NR; ++k)
+            pr[F32 ? 2 * tid + 2 * kThreads * (k >> 1) + (k & 1) : tid + kThreads * k] = own[k];
+        __syncthreads();
+    }
     const uint64_t out0 = uint64_t(blockIdx.x) << a.lb;
-    if (owner_mode) {
+    if (one_bin) {
+        // no bin below bit 12: the group mode's 64 lanes would walk the 512
+        // (256) entries while the rest of the workgroup waits
+        double all = own[0];
+#pragma unroll
+        for (int k = 1; k < (KSUM ? NR : 1); ++k)
+            all += own[k];
+        all = block_sum(all, pr);
+        if (tid == 0)
+            red[out0] = all;
+    } else if (owner_mode) {
         // bins tid, tid + 256, ...; E <= 16 entries each, ascending
 #pragma unroll
         for (int k = 0; k < MAXB; ++k) {
@@ -1261,8 +1270,11 @@ __global__ __launch_bounds__(kThreads) void k_marg_fold(const R *__restrict__ st
             }
         }
     } else if (bin0 < B) {
+        // the bin's entries x_r = deposit(r, restmask), r = gi, gi + G, ...
+        const uint32_t x_step = deposit(uint32_t(G), restmask);
+        const uint32_t d_bin0 = deposit(uint32_t(bin0), a.binmask);
         double sacc = 0.0;
-        uint32_t x = x_first;
+        uint32_t x = deposit(uint32_t(gi), restmask);
         for (int r = gi; r < E; r += G) {
             sacc += pr[d_bin0 | x];
             x = ((x | ~restmask) + x_step) & restmask;

@@ -16,10 +16,11 @@
 // qubits, where it is a chain of latencies (about 340 cycles to read and
 // decode, 430 to address and read the pair, 320 to compute and write, 90 in
 // the barrier), 0.40 us at 11 and 0.90 us at 13, where the vector unit of the
-// one CU bounds it (at 11 it is busy for 95 % of the cycles).  Workgroups of 256 and 512 threads were as fast up to 10
-// qubits and 1.4x and 1.1x slower at 13.  Applying runs of gates to groups of
-// eight amplitudes in registers (one LDS round trip per run) was slower: the
-// uniform dispatch on each gate's target and controls took 0.75 us a gate.
+// one CU bounds it (at 11 it is busy for 95 % of the cycles).  Workgroups of 256
+// and 512 threads were as fast up to 10 qubits and 1.4x and 1.1x slower at 13.
+// Applying runs of gates to groups of eight amplitudes in registers (one LDS
+// round trip per run) was slower: the uniform dispatch on each gate's target
+// and controls took 0.75 us a gate.
 //
 // Steps use the arithmetic of the per-launch kernels: one-target gates as
 // complex 2 x 2 products, blocks of two targets (three below 8 qubits) on the
